@@ -75,6 +75,7 @@ struct DevState {
     // the committed tau, lam, beta0 above).  The commit at the end of the call
     // moves the last draws into the committed fields.
     double hs[2][3];
+    double deferred_b0[4];      // beta0 of the sweeps whose fields wait in the history slots
 };
 
 constexpr unsigned kStatusGamma = 1u;
@@ -104,7 +105,7 @@ struct SweepArgs {
     double *s1, *s2;            // posterior accumulators (layout of x)
     GammaShape g_tau, g_lam;    // Marsaglia-Tsang constants of a_tau + r/2, a_lam + n/2
     double b_tau, b_lam;
-    double rho;
+    double rho, one_minus_rho;
     long long burn_in;
     unsigned long long seed;
     unsigned int instance;
@@ -522,21 +523,35 @@ template <typename Real> struct LatArgs {
     const Real *y;
     int rows, cols;
     int tiles_c;                // tiles per lattice row
+    Real *hist;                 // history slots, n values each
+};
+
+// Deferred accumulation.  S1 and S2 take 32 bytes of traffic per site, as
+// much as everything else a sweep moves, but they are only read after a call.
+// So a call accumulates in groups of sweeps: the fields of a group's first
+// sweeps go to history slots, which the next sweep reads as its input in
+// place of the other state buffer, and the group's last sweep (or the call's)
+// adds them, oldest first, then its own: the same additions in the same
+// order, so the same bits.  The slots lie in the chain's statistics scratch
+// (2n doubles, used only between calls), which holds kHist of them: groups of
+// five FP32 sweeps move 21.6 instead of 44 bytes per site and sweep, groups
+// of three FP64 sweeps 40 instead of 56.  Measured per sweep, 8 neighbours:
+// 4096 x 4096 FP32 172 -> 100 us (2048 x 2048 43.9 -> 32.5), 2048 x 2048 FP64
+// 53.1 -> 50.0 us.
+template <typename Real> constexpr int kHist = 16 / (int)sizeof(Real);
+
+// A sweep's place in its group: the slot holding the field before it and the
+// one its field goes to (-1: the state buffers of its parity), and, for the
+// last sweep of a group, the number of slots to add (-1: a later sweep
+// accumulates).
+struct AccPlan {
+    int in, out, pending;
 };
 
 // Color of a lattice site under the parity coloring of the stencil.
 template <int ST> __host__ __device__ constexpr int parity_color(int pr, int pc)
 {
     return ST == 4 ? ((pr + pc) & 1) : (2 * (pr & 1) + (pc & 1));
-}
-
-// Does the neighbour at offset (dr, dc) of a color-J site have a lower color?
-// (J's parities: 8-neighbour: row parity J>>1, column parity J&1;
-// 4-neighbour: r + c parity J, represented as row parity 0, column parity J.)
-template <int ST, int J> __host__ __device__ constexpr bool lower_nb(int dr, int dc)
-{
-    return ST == 4 ? (parity_color<4>(0, J + dr + dc) < J)
-                   : (parity_color<8>((J >> 1) + dr, (J & 1) + dc) < J);
 }
 
 template <typename Real> struct SiteCtx {
@@ -546,30 +561,157 @@ template <typename Real> struct SiteCtx {
     Real inv_q_full, isd_full;  // 1/Qii and Qii^-1/2 of a site with all k neighbours
     const Real *qtab;           // LDS: 1/Qii for degree 0 .. ST, then Qii^-1/2 (qtab_fill)
     double one_minus_rho, rho;
-    unsigned t;
-    unsigned long long seed;
-    unsigned instance;
 };
 
-// Tile geometry of the fused lattice kernel: TH x TW interior sites, NT
-// threads, the halo (see below); the accumulator read-modify-write of the
-// interior is issued CH sites per thread at a time.
-template <int ST_, int TH_, int TW_, int NT_, int CH_> struct LatCfg {
-    static constexpr int ST = ST_, TH = TH_, TW = TW_, NT = NT_, CH = CH_;
+// Tile geometry of the fused lattice kernel: TH x TW sites, NT threads.
+//
+// The tile is cut into quads of 2 x 2 sites, which hold one site of every
+// color (8 neighbours: color 2 dr + dc of the site at (dr, dc); 4 neighbours:
+// two of each).  A thread owns NQ quads for the whole kernel: their x and y
+// stay in its registers, one pair of loads per quad row, a site finds its
+// neighbours inside the quad there and only the other five (8 neighbours; two
+// for 4) in LDS, and the write-back needs no LDS at all.
+//
+// Around the tile the kernel recomputes the halo sites whose new values the
+// tile needs.  8 neighbours, tile at an even (r0, c0): color 3 reads color 2
+// in its own rows, so color 2 needs one more quad column (c0 + TW); colors
+// 2 and 3 read color 1 in the rows r0 .. r0 + TH, columns c0 - 1 .. c0 + TW + 1;
+// color 1 reads color 0 one column further to each side.  So the halo
+// reaches no row above the tile and one below it, and three columns before
+// and after it; the phases read one site further.  4 neighbours: color 1
+// reads the color-0 sites that touch a side of the tile.
+template <int ST_, int TH_, int TW_, int NT_> struct LatCfg {
+    static constexpr int ST = ST_, TH = TH_, TW = TW_, NT = NT_;
     static constexpr int K = ST == 4 ? 2 : 4;
-    // Halo rings.  With the tile at an even (r0, c0), phase J computes the
-    // color-J sites of the tile grown by K - 1 - J rings and reads one ring
-    // further.  8 neighbours: phase 0's sites (even rows and columns) reach
-    // ring 2 before the tile and ring 3 after it (rows r0 - 2 and
-    // r0 + TH + 2, likewise for columns), so the phases read 3 rings before
-    // and 4 after; 4 neighbours: 2 and 2.  H (rings before, the LDS offset of
-    // the tile) and HH (rings after):
-    static constexpr int H = ST == 8 ? K - 1 : K;
-    static constexpr int HH = K;
-    static constexpr int LH = TH + H + HH, LW = TW + H + HH;
+    static constexpr int QH = TH / 2, QW = TW / 2;
+    static constexpr int NQ = QH * QW / NT;            // quads per thread
+    static constexpr int QR = NT / QW;                 // quad rows of one pass of the threads
+    // staged rows before / after the tile, columns before / after it, and
+    // the LDS column of the tile's first column (even, so that a quad row is
+    // one aligned LDS pair)
+    static constexpr int RB = ST == 8 ? 1 : 2, RA = 2;
+    static constexpr int CB = ST == 8 ? 3 : 2, CA = ST == 8 ? 4 : 2;
+    static constexpr int LC = (CB + 1) / 2 * 2;
+    static constexpr int LH = RB + TH + RA, LW = LC + TW + CA;
+    // cells staged around the tile: RB + RA whole rows, then CB + CA cells of
+    // each tile row
+    static constexpr int RW = CB + TW + CA;
+    static constexpr int NRING = (RB + RA) * RW + TH * (CB + CA);
+    static constexpr int NRL = (NRING + NT - 1) / NT;
+    // halo sites of color J, at most one per thread; the sites of a later
+    // color are a prefix of an earlier color's (halo_pos)
+    static constexpr int halo(int J)
+    {
+        return ST == 4 ? (J == 0 ? 2 * (QH + QW) : 0)
+                       : (J == 0 ? 3 * QH + QW + 3 : J == 1 ? 2 * QH + QW + 2 : J == 2 ? QH : 0);
+    }
+    static constexpr int NH = ST == 4 ? 1 : 3;         // colors with halo sites
     static_assert(TH % 2 == 0 && TW % 2 == 0, "tile sides must be even");
-    static_assert(NT % 64 == 0, "whole wavefronts");
+    static_assert(NT % 64 == 0 && NT % QW == 0 && QH % QR == 0 && NQ * NT == QH * QW,
+                  "whole wavefronts and quad rows");
+    static_assert(halo(0) <= NT, "one halo site per thread");
 };
+
+// Wavefronts per SIMD the sweep kernels are compiled for.  The large tile
+// (two quads per thread) is for large lattices, where the chip is full and
+// residency hides the phases' latency: 64 registers, four blocks per CU, so
+// that the 1024 tiles of a 2048 x 2048 lattice are resident at once (32.3
+// against 34.5 us per sweep with six wavefronts FP32, 44.8 against 46.2 with
+// four FP64).  The small tile (one quad) is for lattices that leave CUs idle:
+// registers for its loads and draws in flight instead (512 x 512 FP64 10.1
+// against 11.5 us with eight).
+template <typename Real, typename Cfg> constexpr int kLatWaves = Cfg::NQ == 1 ? 4 : 8;
+
+// Colors whose normals are drawn while the tile's loads are in flight: all of
+// them where registers allow (small tiles: 10.1 us for 512 x 512 FP64, 10.2
+// with none), one for the large tile (32.3 / 44.8 us for 2048 x 2048 FP32 /
+// FP64 against 32.8 / 45.6 with none).
+template <typename Cfg> constexpr int kDrawAhead = Cfg::NQ == 1 ? Cfg::K : 1;
+
+// y loaded with the tile, or (large FP64 tiles, whose registers it would
+// overflow: 50.0 against 45.6 us for 2048 x 2048) by each color's phase.
+template <typename Real, typename Cfg>
+constexpr bool kYAhead = sizeof(Real) == 4 || Cfg::NQ == 1;
+
+// Position of halo site e relative to the tile's first site: 8 neighbours,
+// the quad whose color-J site it is (its first site; quads (i, QW), then
+// (i, -1), row QH, then (i, QW + 1) and the corner (QH, QW + 1), i = 0 ..
+// QH - 1); 4 neighbours, the color-0 site itself (above, below, left, right).
+template <typename Cfg> __device__ __forceinline__ void halo_pos(int e, int &r, int &c)
+{
+    constexpr int QH = Cfg::QH, QW = Cfg::QW;
+    if constexpr (Cfg::ST == 8) {
+        int i, j;
+        if (e < 2 * QH) {
+            i = e & (QH - 1);
+            j = e < QH ? QW : -1;
+        } else if (e < 2 * QH + QW + 2) {
+            i = QH;
+            j = e - 2 * QH - 1;
+        } else {
+            i = e - 2 * QH - QW - 2;
+            j = QW + 1;
+        }
+        r = 2 * i;
+        c = 2 * j;
+    } else {
+        if (e < 2 * QW) {
+            r = e < QW ? -1 : Cfg::TH;
+            c = e < QW ? 2 * e + 1 : 2 * (e - QW);
+        } else {
+            const int k = e - 2 * QW;
+            r = k < QH ? 2 * k + 1 : 2 * (k - QH);
+            c = k < QH ? -1 : Cfg::TW;
+        }
+    }
+    static_assert(QH >= 1 && (QH & (QH - 1)) == 0, "quad rows a power of two");
+}
+
+// Two adjacent values in memory, at the alignment of one (a row of odd
+// length puts every other row's pairs there; the global loads and stores of
+// this target take any multiple of four bytes).
+template <typename Real> struct Pair;
+template <> struct Pair<float> {
+    typedef float Mem __attribute__((ext_vector_type(2), aligned(4)));
+    typedef float Lds __attribute__((ext_vector_type(2), aligned(8)));
+};
+template <> struct Pair<double> {
+    typedef double Mem __attribute__((ext_vector_type(2), aligned(8)));
+    typedef double Lds __attribute__((ext_vector_type(2), aligned(16)));
+};
+template <typename Real>
+__device__ __forceinline__ typename Pair<Real>::Mem load_pair(const Real *p)
+{
+    return *reinterpret_cast<const typename Pair<Real>::Mem *>(p);
+}
+template <typename Real>
+__device__ __forceinline__ void store_pair(Real *p, typename Pair<Real>::Mem v)
+{
+    *reinterpret_cast<typename Pair<Real>::Mem *>(p) = v;
+}
+
+// The element at byte offset off from a base that is the same in every lane:
+// one 32-bit register of address per lane instead of two, the base in scalar
+// registers.
+template <typename T> __device__ __forceinline__ T *at_bytes(T *base, unsigned off)
+{
+    return reinterpret_cast<T *>(
+        reinterpret_cast<std::conditional_t<std::is_const_v<T>, const char, char> *>(base) + off);
+}
+
+// A value that is the same in every lane, moved to scalar registers.
+__device__ __forceinline__ float uniform_value(float v)
+{
+    return __builtin_bit_cast(float,
+                              __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ double uniform_value(double v)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
 
 // 1/Qii and Qii^-1/2 for every degree 0 .. ST into the LDS table (threads
 // 0 .. ST), with site_scales, so a lookup is bitwise the per-site value.  The
@@ -582,298 +724,464 @@ __device__ __forceinline__ void qtab_fill(Real *qtab, Real tau, Real lam)
         site_scales<Real>(tau, lam, d, qtab[d], qtab[ST + 1 + d]);
 }
 
-// One site of Algorithm 1 on the LDS tile: neighbour sum in ascending
-// original-id order, conditional mean and precision, the draw with the
-// site's standard normal z; for interior sites also the q / sse terms.
-// Cells of the tile outside the lattice hold 0 (lattice_load), so the
-// neighbour sum adds every stencil cell: a missing neighbour adds 0, which
-// leaves each partial sum of the in-lattice neighbours unchanged.
+// The neighbours of a site in ascending original-id order.
+template <int ST> struct Stencil;
+template <> struct Stencil<8> {
+    static constexpr int dr[8] = {-1, -1, -1, 0, 0, 1, 1, 1};
+    static constexpr int dc[8] = {-1, 0, 1, -1, 1, -1, 0, 1};
+};
+template <> struct Stencil<4> {
+    static constexpr int dr[4] = {-1, 0, 0, 1};
+    static constexpr int dc[4] = {0, -1, 1, 0};
+};
+
+// Which rows and columns around a site at (r, c) of a rows x cols lattice
+// exist (a quad: rows r - 1 .. r + 2, columns c - 1 .. c + 2; the quad's first
+// site is in the lattice when row 0 and column 0 are).
+struct Around {
+    bool row[4], col[4];
+    __device__ __forceinline__ Around(int r, int c, int rows, int cols)
+    {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            row[k] = r + k - 1 >= 0 && r + k - 1 < rows;
+            col[k] = c + k - 1 >= 0 && c + k - 1 < cols;
+        }
+    }
+    // site (dr, dc) of the quad
+    __device__ __forceinline__ bool has(int dr, int dc) const
+    {
+        return row[dr + 1] && col[dc + 1];
+    }
+    // its neighbours in the lattice
+    template <int ST> __device__ __forceinline__ int degree(int dr, int dc) const
+    {
+        const int nr = 1 + (int)row[dr] + (int)row[dr + 2];
+        const int nc = 1 + (int)col[dc] + (int)col[dc + 2];
+        return ST == 8 ? nr * nc - 1 : nr + nc - 2;
+    }
+};
+
+// FP64 sums of a tile's sites: d^2 over the edges, D_ii x_i^2 (interior
+// tiles: x_i^2, every degree being ST), and the residuals.
+struct LatRed {
+    double edge = 0.0, dsq = 0.0, sse = 0.0, rsum = 0.0;
+    // Take the sums where they are written: the compiler otherwise moves the
+    // terms to the end of the kernel, where they are first needed, and holds
+    // every neighbour value in registers until then.
+    __device__ __forceinline__ void settle()
+    {
+        asm volatile("" : "+v"(edge), "+v"(dsq), "+v"(sse), "+v"(rsum));
+    }
+};
+
+// Standard normal of the site at (r, c).  V2: the paired contract -- the
+// sites of a color, ranked by original id, share one Philox block per rank
+// pair, the cosine branch for the first, the sine branch for the second.
+// With the lattice width a multiple of 4 every row holds an even number of
+// sites of each of its colors, so the pairs are (r, c) and (r, c + 2) with bit
+// 1 of c clear, keyed by the id of (r, c).
+template <typename Real, bool V2>
+__device__ __forceinline__ Real lattice_normal(const SweepArgs &a, unsigned t, int r, int c,
+                                               int cols)
+{
+    const unsigned id = (unsigned)r * (unsigned)cols + (unsigned)(V2 ? c & ~2 : c);
+    const Words4 w = draw_words(a.seed, id, t, a.instance, 0u);
+    if constexpr (V2)
+        return site_normal_branch<Real>(w, (c & 2) != 0);
+    else
+        return site_normal<Real>(w);
+}
+
+// Site S = 2 dr + dc of a quad: neighbour sum in ascending original-id
+// order, conditional mean and precision, the draw with the standard normal z,
+// and the q / sse terms.  p: the LDS cell of the quad's first site; q: the
+// quad's values (those of earlier phases already new).  Cells outside the
+// lattice hold 0, so the sum adds every stencil cell: a missing neighbour
+// adds 0, which leaves the partial sums of the in-lattice ones unchanged.
 // INTERIOR: the tile and its halo lie inside the lattice, so every site has
 // all its neighbours (compile-time flags).
-template <typename Real, typename Cfg, int J, bool INTERIOR, bool B0>
-__device__ __forceinline__ void lattice_site(Real *xs, Real yv, Real z, int r, int c, int r0,
-                                             int c0, int rows, int cols, const SiteCtx<Real> &sc,
-                                             Red &rd)
+template <typename Real, typename Cfg, int S, bool INTERIOR, bool B0>
+__device__ __forceinline__ Real quad_site(const Real *p, const Real (&q)[4], Real yv, Real z,
+                                          const Around &in, const SiteCtx<Real> &sc, LatRed &rd)
 {
-    constexpr int ST = Cfg::ST, H = Cfg::H, LW = Cfg::LW;
-    Real *p = xs + (r - r0 + H) * LW + (c - c0 + H);
-    const bool up = INTERIOR || r > 0, dn = INTERIOR || r + 1 < rows;
-    const bool lf = INTERIOR || c > 0, rt = INTERIOR || c + 1 < cols;
+    constexpr int ST = Cfg::ST, LW = Cfg::LW, SR = S >> 1, SC = S & 1;
+    constexpr int J = parity_color<ST>(SR, SC);
+    using N = Stencil<ST>;
+    Real v[ST];
+#pragma unroll
+    for (int k = 0; k < ST; ++k) {
+        const int tr = SR + N::dr[k], tc = SC + N::dc[k];
+        v[k] = tr >= 0 && tr < 2 && tc >= 0 && tc < 2 ? q[2 * (tr & 1) + (tc & 1)]
+                                                      : p[tr * LW + tc];
+    }
     Real s = (Real)0;
-    if (ST == 8) s += p[-LW - 1];
-    s += p[-LW];
-    if (ST == 8) s += p[-LW + 1];
-    s += p[-1];
-    s += p[1];
-    if (ST == 8) s += p[LW - 1];
-    s += p[LW];
-    if (ST == 8) s += p[LW + 1];
-
+#pragma unroll
+    for (int k = 0; k < ST; ++k)
+        s += v[k];
     Real inv_q, isd;
+    int deg = ST;
     if constexpr (INTERIOR) {
         inv_q = sc.inv_q_full;
         isd = sc.isd_full;
     } else {
-        const int nr = 1 + (int)up + (int)dn, nc = 1 + (int)lf + (int)rt;
-        const int deg = ST == 8 ? nr * nc - 1 : nr + nc - 2;
+        deg = in.degree<ST>(SR, SC);
         inv_q = sc.qtab[deg];
         isd = sc.qtab[ST + 1 + deg];
     }
     const Real yeff = B0 ? yv - sc.beta0_r : yv;
     const Real xn = site_draw<Real>(yeff, s, z, sc.lam, sc.tau_rho, inv_q, isd);
-    *p = xn;
-
-    if (r >= r0 && r < r0 + Cfg::TH && c >= c0 && c < c0 + Cfg::TW) {
-        const double xd = (double)xn;
-        double edge = 0.0;
-#define GMRF_EDGE(cond, dr, dc, off)                                                  \
-    if (lower_nb<ST, J>(dr, dc) && (cond)) {                                          \
-        const double d = xd - (double)p[off];                                         \
-        edge += d * d;                                                                \
-    }
-        if (ST == 8) GMRF_EDGE(up && lf, -1, -1, -LW - 1)
-        GMRF_EDGE(up, -1, 0, -LW)
-        if (ST == 8) GMRF_EDGE(up && rt, -1, 1, -LW + 1)
-        GMRF_EDGE(lf, 0, -1, -1)
-        GMRF_EDGE(rt, 0, 1, 1)
-        if (ST == 8) GMRF_EDGE(dn && lf, 1, -1, LW - 1)
-        GMRF_EDGE(dn, 1, 0, LW)
-        if (ST == 8) GMRF_EDGE(dn && rt, 1, 1, LW + 1)
-#undef GMRF_EDGE
-        int deg = ST;
-        if constexpr (!INTERIOR) {
-            const int nr = 1 + (int)up + (int)dn, nc = 1 + (int)lf + (int)rt;
-            deg = ST == 8 ? nr * nc - 1 : nr + nc - 2;
-        }
-        rd.q += sc.one_minus_rho * (double)deg * xd * xd + sc.rho * edge;
-        if constexpr (B0) {
-            const double rr = (double)yv - sc.beta0 - xd;
-            rd.sse += rr * rr;
-            rd.rsum += rr;
-        } else {
-            const double rr = (double)yv - xd;
-            rd.sse += rr * rr;
+    const double xd = (double)xn;
+#pragma unroll
+    for (int k = 0; k < ST; ++k) {
+        const int tr = SR + N::dr[k], tc = SC + N::dc[k];
+        if (parity_color<ST>(tr + 2, tc + 2) < J && (INTERIOR || in.has(tr, tc))) {
+            const double d = xd - (double)v[k];
+            rd.edge += d * d;
         }
     }
+    rd.dsq += (INTERIOR ? xd : (double)deg * xd) * xd;
+    const double rr = B0 ? (double)yv - sc.beta0 - xd : (double)yv - xd;
+    rd.sse += rr * rr;
+    if constexpr (B0)
+        rd.rsum += rr;
+    return xn;
 }
 
-// Quotient and remainder of idx by d (0 <= idx < 2^24, d >= 1) through an FP32
-// reciprocal with a one-step correction.
-__device__ __forceinline__ int div_small(int idx, int d, float rcp, int &rem)
+// The new value of the halo site at cell p (lattice position (r, c)), whose
+// owner adds its terms.
+template <typename Real, typename Cfg, bool INTERIOR, bool B0>
+__device__ __forceinline__ Real halo_site(const Real *p, Real yv, Real z, int r, int c, int rows,
+                                          int cols, const SiteCtx<Real> &sc)
 {
-    int qt = (int)((float)idx * rcp);
-    qt -= (qt * d > idx);
-    qt += ((qt + 1) * d <= idx);
-    rem = idx - qt * d;
-    return qt;
+    constexpr int ST = Cfg::ST;
+    using N = Stencil<ST>;
+    Real s = (Real)0;
+#pragma unroll
+    for (int k = 0; k < ST; ++k)
+        s += p[N::dr[k] * Cfg::LW + N::dc[k]];
+    Real inv_q = sc.inv_q_full, isd = sc.isd_full;
+    if constexpr (!INTERIOR) {
+        const int deg = Around(r, c, rows, cols).degree<ST>(0, 0);
+        inv_q = sc.qtab[deg];
+        isd = sc.qtab[ST + 1 + deg];
+    }
+    const Real yeff = B0 ? yv - sc.beta0_r : yv;
+    return site_draw<Real>(yeff, s, z, sc.lam, sc.tau_rho, inv_q, isd);
 }
 
-// The color-J sites of the tile grown by E = k-1-J rings: rows ra .. rb - 1
-// and columns ca .. cb - 1 (8 neighbours: ra and ca moved to the parities of
-// J), nR rows of at most nC sites each.  Unit idx = R nC + C of a phase is
-// the site (ra + R, ca + ((r + ca + J) & 1) + 2 C) for 4 neighbours and
-// (ra + 2 R, ca + 2 C) for 8.
-struct PhaseGeom {
-    int ra, rb, ca, cb, nR, nC;
+// Where a tile lies.
+struct TileAt {
+    int r0, c0, rows, cols;
+    __device__ __forceinline__ size_t first() const { return (size_t)r0 * cols + c0; }
+    template <typename T> __device__ __forceinline__ unsigned row_bytes() const
+    {
+        return (unsigned)sizeof(T) * (unsigned)cols;
+    }
 };
 
-template <typename Cfg, int J>
-__device__ __forceinline__ PhaseGeom phase_geom(int r0, int c0, int rows, int cols)
+// Widest lattice whose tiles take 32-bit byte offsets from their first site
+// (TH + RA rows of doubles); wider ones take the general path.
+constexpr int kOffsetCols = 1 << 22;
+
+// A thread's part of a tile: its quads and its halo site of each color.  The
+// tile kernels draw the normals of the first kDrawAhead colors while the loads
+// of the tile and of the previous sweep's partials are in flight.
+template <typename Real, typename Cfg> struct QuadRegs {
+    Real x[Cfg::NQ][4], y[Cfg::NQ][4], z[Cfg::NQ][4];
+    Real yh[Cfg::NH], zh[Cfg::NH];
+};
+
+// The thread's index as a value the compiler does not connect with earlier
+// uses: the stages of a tile derive their offsets from it again (a few
+// integer operations) instead of keeping them in registers in between.
+template <typename Cfg> __device__ __forceinline__ int thread_again()
 {
-    constexpr int E = Cfg::K - 1 - J;
-    PhaseGeom g;
-    g.ra = max(r0 - E, 0);
-    g.rb = min(r0 + Cfg::TH + E, rows);
-    g.ca = max(c0 - E, 0);
-    g.cb = min(c0 + Cfg::TW + E, cols);
-    if constexpr (Cfg::ST == 8) {
-        g.ra += ((g.ra & 1) != (J >> 1));
-        g.ca += ((g.ca & 1) != (J & 1));
-        g.nR = g.rb > g.ra ? (g.rb - g.ra + 1) >> 1 : 0;
-    } else {
-        g.nR = g.rb > g.ra ? g.rb - g.ra : 0;
-    }
-    g.nC = g.cb > g.ca ? (g.cb - g.ca + 1) >> 1 : 0;
-    return g;
+    int tid = (int)threadIdx.x;
+    if constexpr (Cfg::NQ > 1)
+        asm volatile("" : "+v"(tid));
+    return tid;
 }
 
-// Most units of a phase of the grown tile (phase 0 grows the most).
-template <typename Cfg> constexpr int phase_units(int J)
+// First site of thread tid's quad i, relative to the tile.
+template <typename Cfg> __device__ __forceinline__ int quad_row(int tid, int i)
 {
-    return Cfg::ST == 8 ? (Cfg::TH / 2 + Cfg::K - 1 - J) * (Cfg::TW / 2 + Cfg::K - 1 - J)
-                        : (Cfg::TH + 2 * (Cfg::K - 1 - J)) *
-                              ((Cfg::TW + 2 * (Cfg::K - 1 - J) + 1) / 2);
+    return 2 * (tid / Cfg::QW + i * Cfg::QR);
+}
+template <typename Cfg> __device__ __forceinline__ int quad_col(int tid)
+{
+    return 2 * (tid % Cfg::QW);
 }
 
-// Phase J: every color-J site of the grown tile.  The iteration count per
-// thread has a compile-time bound, so the y loads of all of a thread's sites
-// are issued before the first site is computed; mid() runs between the
-// loads and the sites (work that hides their latency).  zin: the sites'
-// normals, drawn ahead by lattice_normals at the units' indices (paired
-// random-number contract), or NULL to draw each site's own block here.
-template <typename Real, typename Cfg, int J, bool INTERIOR, bool B0, typename Mid>
-__device__ __forceinline__ void lattice_phase(Real *xs, const Real *__restrict__ y, int r0,
-                                              int c0, int rows, int cols, const SiteCtx<Real> &sc,
-                                              Red &rd, const Real *zin, Mid &&mid)
+// Byte offset of thread tid's quad i from the tile's first site.
+template <typename T, typename Cfg>
+__device__ __forceinline__ unsigned quad_offset(int tid, int i, const TileAt &at)
 {
-    constexpr int NT = Cfg::NT;
-    constexpr int NI = (phase_units<Cfg>(J) + NT - 1) / NT;
-    const PhaseGeom g = phase_geom<Cfg, J>(r0, c0, rows, cols);
-    const int total = g.nR * g.nC;
-    const float rcp = 1.0f / (float)max(g.nC, 1);
-    int rr[NI], cc[NI];
-    Real yv[NI];
+    return (unsigned)sizeof(T) *
+           ((unsigned)quad_row<Cfg>(tid, i) * (unsigned)at.cols + (unsigned)quad_col<Cfg>(tid));
+}
+
+// The thread's quads of a row-major field (sites outside the lattice: 0,
+// their loads from an address clamped into it).
+template <typename Real, typename Cfg, bool INTERIOR>
+__device__ __forceinline__ void load_quads(Real (&v)[Cfg::NQ][4], const Real *__restrict__ f,
+                                           const TileAt &at)
+{
+    const int tid = thread_again<Cfg>();
 #pragma unroll
-    for (int k = 0; k < NI; ++k) {
-        const int idx = (int)threadIdx.x + k * NT;
-        int C;
-        const int R = div_small(idx, max(g.nC, 1), rcp, C);
+    for (int i = 0; i < Cfg::NQ; ++i) {
+        const int r = at.r0 + quad_row<Cfg>(tid, i), c = at.c0 + quad_col<Cfg>(tid);
+        if constexpr (INTERIOR) {
+            const unsigned off = quad_offset<Real, Cfg>(tid, i, at);
+            const auto top = load_pair<Real>(at_bytes(f + at.first(), off));
+            const auto bot = load_pair<Real>(at_bytes(f + at.first(), off + at.row_bytes<Real>()));
+            v[i][0] = top.x;
+            v[i][1] = top.y;
+            v[i][2] = bot.x;
+            v[i][3] = bot.y;
+        } else {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int rr = r + (s >> 1), cc = c + (s & 1);
+                v[i][s] = f[(size_t)min(rr, at.rows - 1) * at.cols + min(cc, at.cols - 1)];
+                if (rr >= at.rows || cc >= at.cols)
+                    v[i][s] = (Real)0;
+            }
+        }
+    }
+}
+
+// The color-J values of the thread's quads.
+template <typename Real, typename Cfg, int J, bool INTERIOR>
+__device__ __forceinline__ void load_color(Real (&v)[Cfg::NQ][4], const Real *__restrict__ f,
+                                           const TileAt &at)
+{
+    const int tid = thread_again<Cfg>();
+#pragma unroll
+    for (int i = 0; i < Cfg::NQ; ++i)
+#pragma unroll
+        for (int S = 0; S < 4; ++S)
+            if (parity_color<Cfg::ST>(S >> 1, S & 1) == J) {
+                if constexpr (INTERIOR) {
+                    const unsigned off = quad_offset<Real, Cfg>(tid, i, at) +
+                                         (S >> 1) * at.row_bytes<Real>() +
+                                         (S & 1) * (unsigned)sizeof(Real);
+                    v[i][S] = *at_bytes(f + at.first(), off);
+                } else {
+                    const int r = at.r0 + quad_row<Cfg>(tid, i) + (S >> 1);
+                    const int c = at.c0 + quad_col<Cfg>(tid) + (S & 1);
+                    v[i][S] = f[(size_t)min(r, at.rows - 1) * at.cols + min(c, at.cols - 1)];
+                }
+            }
+}
+
+// Ring cell idx: position relative to the tile.
+template <typename Cfg> __device__ __forceinline__ void ring_pos(int idx, int &r, int &c)
+{
+    constexpr int TOP = (Cfg::RB + Cfg::RA) * Cfg::RW, SIDE = Cfg::CB + Cfg::CA;
+    if (idx < TOP) {
+        const int k = idx / Cfg::RW;
+        r = k < Cfg::RB ? k - Cfg::RB : k - Cfg::RB + Cfg::TH;
+        c = idx - k * Cfg::RW - Cfg::CB;
+    } else {
+        r = (idx - TOP) / SIDE;
+        const int k = idx - TOP - r * SIDE;
+        c = k < Cfg::CB ? k - Cfg::CB : k - Cfg::CB + Cfg::TW;
+    }
+}
+
+// y of the thread's halo site of color j.
+template <typename Real, typename Cfg, bool INTERIOR>
+__device__ __forceinline__ Real load_halo_y(const Real *__restrict__ y, int j, const TileAt &at)
+{
+    int r, c;
+    halo_pos<Cfg>(thread_again<Cfg>(), r, c);
+    if (Cfg::ST == 8) {
+        r += j >> 1;
+        c += j & 1;
+    }
+    if constexpr (INTERIOR) {
+        const unsigned off =
+            (unsigned)sizeof(Real) *
+            ((unsigned)(r + Cfg::RB) * (unsigned)at.cols + (unsigned)(c + Cfg::CB));
+        return *at_bytes(y + (at.first() - (size_t)Cfg::RB * at.cols - Cfg::CB), off);
+    } else {
+        return y[(size_t)min(max(at.r0 + r, 0), at.rows - 1) * at.cols +
+                 min(max(at.c0 + c, 0), at.cols - 1)];
+    }
+}
+
+// The global loads of the tile (the field with its ring, and if kYAhead y of
+// the quads and of the halo sites), issued before any is used.
+template <typename Real, typename Cfg, bool INTERIOR>
+__device__ __forceinline__ void tile_load(QuadRegs<Real, Cfg> &t, Real (&ring)[Cfg::NRL],
+                                          const Real *__restrict__ src,
+                                          const Real *__restrict__ y, const TileAt &at)
+{
+    load_quads<Real, Cfg, INTERIOR>(t.x, src, at);
+#pragma unroll
+    for (int k = 0; k < Cfg::NRL; ++k) {
         int r, c;
-        if constexpr (Cfg::ST == 8) {
-            r = g.ra + 2 * R;
-            c = g.ca + 2 * C;
+        ring_pos<Cfg>(min((int)threadIdx.x + k * Cfg::NT, Cfg::NRING - 1), r, c);
+        if constexpr (INTERIOR) {
+            const unsigned off = (unsigned)sizeof(Real) * ((unsigned)(r + Cfg::RB) * (unsigned)at.cols +
+                                                           (unsigned)(c + Cfg::CB));
+            ring[k] = *at_bytes(src + (at.first() - (size_t)Cfg::RB * at.cols - Cfg::CB), off);
         } else {
-            r = g.ra + R;
-            c = g.ca + ((r + g.ca + J) & 1) + 2 * C;
+            r += at.r0;
+            c += at.c0;
+            const int rc = min(max(r, 0), at.rows - 1), cc = min(max(c, 0), at.cols - 1);
+            ring[k] = src[(size_t)rc * at.cols + cc];
+            if (r != rc || c != cc)
+                ring[k] = (Real)0;
         }
-        const bool ok = idx < total && c < g.cb;
-        rr[k] = ok ? r : -1;
-        cc[k] = c;
-        // clamped address: always inside the lattice, used only when ok
-        const int rc = min(max(r, 0), rows - 1), ccl = min(max(c, 0), cols - 1);
-        yv[k] = y[(size_t)rc * cols + ccl];
     }
-    mid();
+    if constexpr (kYAhead<Real, Cfg>) {
+        load_quads<Real, Cfg, INTERIOR>(t.y, y, at);
 #pragma unroll
-    for (int k = 0; k < NI; ++k)
-        if (rr[k] >= 0) {
-            Real z;
-            if (zin) {
-                z = zin[(int)threadIdx.x + k * NT];
-            } else {
-                const unsigned site = (unsigned)rr[k] * (unsigned)cols + (unsigned)cc[k];
-                z = site_normal<Real>(draw_words(sc.seed, site, sc.t, sc.instance, 0u));
-            }
-            lattice_site<Real, Cfg, J, INTERIOR, B0>(xs, yv[k], z, rr[k], cc[k], r0, c0, rows,
-                                                     cols, sc, rd);
-        }
+        for (int j = 0; j < Cfg::NH; ++j)
+            if ((int)threadIdx.x < Cfg::halo(j))
+                t.yh[j] = load_halo_y<Real, Cfg, INTERIOR>(y, j, at);
+    }
 }
 
-// The normals of phase J's sites under the paired random-number contract,
-// into zb at the phase's unit indices.  The sites of a color, ranked by
-// original id, share one Philox block per rank pair (2m, 2m + 1): the
-// cosine branch for the first, the sine branch for the second.  With the
-// lattice width a multiple of 4 every row holds an even number of sites of
-// each of its colors, so the pairs are (r, c) and (r, c + 2) with bit 1 of c
-// clear, keyed by the id of (r, c).  A thread takes pair slots here (one
-// block and one Box-Muller radius for two sites) and the site updates take
-// one site per thread, so the update reads the tile with the stride of the
-// unpaired phase; a slot cut by the edge of the grown tile stores the one
-// normal inside.
-template <typename Real, typename Cfg, int J>
-__device__ __forceinline__ void lattice_normals(Real *zb, int r0, int c0, int rows, int cols,
-                                                const SiteCtx<Real> &sc)
+// LDS cell of the tile's site at relative position (r, c).
+template <typename Cfg> __device__ __forceinline__ int tile_cell(int r, int c)
 {
-    constexpr int E = Cfg::K - 1 - J;
-    constexpr int NT = Cfg::NT;
-    static_assert(Cfg::TW % 4 == 0, "pair slots need tile columns at multiples of 4");
-    // rows of the grown tile that hold color-J sites, and pair slots per row
-    // (c0 is a multiple of 4, so columns c0 - E .. c0 + TW + E - 1 meet at
-    // most TW / 4 + 2 slots)
-    constexpr int MR = Cfg::ST == 8 ? Cfg::TH / 2 + E : Cfg::TH + 2 * E;
-    constexpr int MP = Cfg::TW / 4 + 2;
-    constexpr int NI = (MR * MP + NT - 1) / NT;
-    const PhaseGeom g = phase_geom<Cfg, J>(r0, c0, rows, cols);
-    const int pa = g.ca >> 2;
-    int nP;
-    if constexpr (Cfg::ST == 8) {
-        const int cl = g.cb - 1 - (((g.cb - 1) & 1) != (J & 1));   // last column of parity J & 1
-        nP = cl >= g.ca ? (cl >> 2) - pa + 1 : 0;
-    } else {
-        nP = g.cb > g.ca ? ((g.cb - 1) >> 2) - pa + 1 : 0;
-    }
-    const int total = g.nR * nP;
-    const float rcp = 1.0f / (float)max(nP, 1);
+    return (r + Cfg::RB) * Cfg::LW + c + Cfg::LC;
+}
+
+template <typename Real, typename Cfg>
+__device__ __forceinline__ void stage_quads(Real *xs, const Real (&x)[Cfg::NQ][4])
+{
+    using L = typename Pair<Real>::Lds;
+    const int tid = thread_again<Cfg>();
 #pragma unroll
-    for (int k = 0; k < NI; ++k) {
-        const int idx = (int)threadIdx.x + k * NT;
-        if (idx < total) {
-            int P;
-            const int R = div_small(idx, max(nP, 1), rcp, P);
-            const int r = Cfg::ST == 8 ? g.ra + 2 * R : g.ra + R;
-            const int off = Cfg::ST == 8 ? (J & 1) : ((r + J) & 1);
-            const int c = 4 * (pa + P) + off;
-            const bool in1 = c >= g.ca && c < g.cb, in2 = c + 2 >= g.ca && c + 2 < g.cb;
-            if (in1 || in2) {
-                const unsigned key = (unsigned)r * (unsigned)cols + (unsigned)c;
-                Real zc, zs;
-                site_normal_pair<Real>(draw_words(sc.seed, key, sc.t, sc.instance, 0u), zc, zs);
-                Real *const zrow = zb + R * g.nC;
-                if (in1)
-                    zrow[(c - g.ca) >> 1] = zc;
-                if (in2)
-                    zrow[(c + 2 - g.ca) >> 1] = zs;
+    for (int i = 0; i < Cfg::NQ; ++i) {
+        Real *const p = xs + tile_cell<Cfg>(quad_row<Cfg>(tid, i), quad_col<Cfg>(tid));
+        *reinterpret_cast<L *>(p) = L{x[i][0], x[i][1]};
+        *reinterpret_cast<L *>(p + Cfg::LW) = L{x[i][2], x[i][3]};
+    }
+}
+
+template <typename Real, typename Cfg>
+__device__ __forceinline__ void stage_tile(Real *xs, const QuadRegs<Real, Cfg> &t,
+                                           const Real (&ring)[Cfg::NRL])
+{
+    stage_quads<Real, Cfg>(xs, t.x);
+#pragma unroll
+    for (int k = 0; k < Cfg::NRL; ++k) {
+        const int idx = (int)threadIdx.x + k * Cfg::NT;
+        int r, c;
+        ring_pos<Cfg>(idx, r, c);
+        if (k < Cfg::NRL - 1 || idx < Cfg::NRING)
+            xs[tile_cell<Cfg>(r, c)] = ring[k];
+    }
+}
+
+// Normals of the color-J sites of the thread (its quads, and its halo site
+// if HALO).
+template <typename Real, typename Cfg, int J, bool INTERIOR, bool V2, bool HALO>
+__device__ __forceinline__ void draw_normals(QuadRegs<Real, Cfg> &t, const TileAt &at,
+                                             const SweepArgs &a, unsigned sweep)
+{
+    const int tid = thread_again<Cfg>();
+#pragma unroll
+    for (int S = 0; S < 4; ++S)
+        if (parity_color<Cfg::ST>(S >> 1, S & 1) == J)
+#pragma unroll
+            for (int i = 0; i < Cfg::NQ; ++i) {
+                const int r = at.r0 + quad_row<Cfg>(tid, i) + (S >> 1);
+                const int c = at.c0 + quad_col<Cfg>(tid) + (S & 1);
+                if (INTERIOR || (r < at.rows && c < at.cols))
+                    t.z[i][S] = lattice_normal<Real, V2>(a, sweep, r, c, at.cols);
+            }
+    if constexpr (HALO && Cfg::halo(J) > 0) {
+        if ((int)threadIdx.x < Cfg::halo(J)) {
+            int r, c;
+            halo_pos<Cfg>(tid, r, c);
+            if (Cfg::ST == 8) {
+                r += J >> 1;
+                c += J & 1;
+            }
+            t.zh[J] = lattice_normal<Real, V2>(a, sweep, at.r0 + r, at.c0 + c, at.cols);
+        }
+    }
+}
+
+// Sites S of color J in the thread's quads.
+template <typename Real, typename Cfg, int S, bool INTERIOR, bool B0, bool HALO>
+__device__ __forceinline__ void quad_sites(Real *xs, QuadRegs<Real, Cfg> &t, const TileAt &at,
+                                           const SiteCtx<Real> &sc, LatRed &rd)
+{
+    const int tid = thread_again<Cfg>();
+#pragma unroll
+    for (int i = 0; i < Cfg::NQ; ++i) {
+        const int qr = quad_row<Cfg>(tid, i), qc = quad_col<Cfg>(tid);
+        const Around in(at.r0 + qr, at.c0 + qc, at.rows, at.cols);
+        if (INTERIOR || in.has(S >> 1, S & 1)) {
+            Real *const p = xs + tile_cell<Cfg>(qr, qc);
+            t.x[i][S] = quad_site<Real, Cfg, S, INTERIOR, B0>(p, t.x[i], t.y[i][S], t.z[i][S], in,
+                                                              sc, rd);
+            p[(S >> 1) * Cfg::LW + (S & 1)] = t.x[i][S];
+        }
+        if (HALO && Cfg::NQ > 1)
+            rd.settle();
+    }
+}
+
+// Phase J: every color-J site of the tile, and of its halo if HALO.
+template <typename Real, typename Cfg, int J, bool INTERIOR, bool B0, bool HALO>
+__device__ __forceinline__ void lattice_phase(Real *xs, QuadRegs<Real, Cfg> &t, const TileAt &at,
+                                              const SiteCtx<Real> &sc, LatRed &rd)
+{
+    quad_sites<Real, Cfg, J, INTERIOR, B0, HALO>(xs, t, at, sc, rd);
+    if constexpr (Cfg::ST == 4)
+        quad_sites<Real, Cfg, 3 - J, INTERIOR, B0, HALO>(xs, t, at, sc, rd);
+    if constexpr (HALO && Cfg::halo(J) > 0) {
+        if ((int)threadIdx.x < Cfg::halo(J)) {
+            int hr, hc;
+            halo_pos<Cfg>(thread_again<Cfg>(), hr, hc);
+            if (Cfg::ST == 8) {
+                hr += J >> 1;
+                hc += J & 1;
+            }
+            const int r = at.r0 + hr, c = at.c0 + hc;
+            if (INTERIOR || (r >= 0 && r < at.rows && c >= 0 && c < at.cols)) {
+                Real *const p = xs + tile_cell<Cfg>(hr, hc);
+                *p = halo_site<Real, Cfg, INTERIOR, B0>(p, t.yh[J], t.zh[J], r, c, at.rows,
+                                                        at.cols, sc);
             }
         }
     }
 }
 
-// The k color phases of one tile, separated by LDS barriers.  V2: the chain
-// draws by the paired contract; zb then holds two buffers of
-// phase_units<Cfg>(0) normals, and the caller has drawn phase 0's into the
-// first and synchronised.  Each phase draws the next phase's normals into
-// the other buffer between its y loads and its site updates; the barrier
-// that ends the phase publishes them.
-template <typename Real, typename Cfg, bool INTERIOR, bool B0, bool V2>
-__device__ __forceinline__ void lattice_phases(Real *xs, const Real *__restrict__ y, int r0,
-                                               int c0, int rows, int cols, const SiteCtx<Real> &sc,
-                                               Red &rd, Real *zb)
+// The k color phases of one tile, separated by LDS barriers (none after the
+// last: the write-back reads registers).  ahead(J): what phase J needs
+// before its updates (its normals and y where they are not there already).
+template <typename Real, typename Cfg, bool INTERIOR, bool B0, bool HALO, typename Ahead>
+__device__ __forceinline__ Red lattice_phases(Real *xs, QuadRegs<Real, Cfg> &t, const TileAt &at,
+                                              const SiteCtx<Real> &sc, Ahead &&ahead)
 {
-    constexpr int ZN = phase_units<Cfg>(0);
-    auto none = [] {};
-    if constexpr (V2) {
-        lattice_phase<Real, Cfg, 0, INTERIOR, B0>(
-            xs, y, r0, c0, rows, cols, sc, rd, zb,
-            [&] { lattice_normals<Real, Cfg, 1>(zb + ZN, r0, c0, rows, cols, sc); });
+    LatRed rd;
+    ahead(std::integral_constant<int, 0>{});
+    lattice_phase<Real, Cfg, 0, INTERIOR, B0, HALO>(xs, t, at, sc, rd);
+    lds_barrier();
+    ahead(std::integral_constant<int, 1>{});
+    lattice_phase<Real, Cfg, 1, INTERIOR, B0, HALO>(xs, t, at, sc, rd);
+    if constexpr (Cfg::K == 4) {
         lds_barrier();
-        if constexpr (Cfg::K == 4) {
-            lattice_phase<Real, Cfg, 1, INTERIOR, B0>(
-                xs, y, r0, c0, rows, cols, sc, rd, zb + ZN,
-                [&] { lattice_normals<Real, Cfg, 2>(zb, r0, c0, rows, cols, sc); });
-            lds_barrier();
-            lattice_phase<Real, Cfg, 2, INTERIOR, B0>(
-                xs, y, r0, c0, rows, cols, sc, rd, zb,
-                [&] { lattice_normals<Real, Cfg, 3>(zb + ZN, r0, c0, rows, cols, sc); });
-            lds_barrier();
-            lattice_phase<Real, Cfg, 3, INTERIOR, B0>(xs, y, r0, c0, rows, cols, sc, rd,
-                                                      zb + ZN, none);
-            lds_barrier();
-        } else {
-            lattice_phase<Real, Cfg, 1, INTERIOR, B0>(xs, y, r0, c0, rows, cols, sc, rd,
-                                                      zb + ZN, none);
-            lds_barrier();
-        }
-    } else {
-        const Real *const nz = nullptr;
-        lattice_phase<Real, Cfg, 0, INTERIOR, B0>(xs, y, r0, c0, rows, cols, sc, rd, nz, none);
+        ahead(std::integral_constant<int, 2>{});
+        lattice_phase<Real, Cfg, 2, INTERIOR, B0, HALO>(xs, t, at, sc, rd);
         lds_barrier();
-        lattice_phase<Real, Cfg, 1, INTERIOR, B0>(xs, y, r0, c0, rows, cols, sc, rd, nz, none);
-        lds_barrier();
-        if constexpr (Cfg::K == 4) {
-            lattice_phase<Real, Cfg, 2, INTERIOR, B0>(xs, y, r0, c0, rows, cols, sc, rd, nz,
-                                                      none);
-            lds_barrier();
-            lattice_phase<Real, Cfg, 3, INTERIOR, B0>(xs, y, r0, c0, rows, cols, sc, rd, nz,
-                                                      none);
-            lds_barrier();
-        }
+        ahead(std::integral_constant<int, 3>{});
+        lattice_phase<Real, Cfg, 3, INTERIOR, B0, HALO>(xs, t, at, sc, rd);
     }
-}
-
-// LDS normals of a V2 tile: two phase buffers (one element otherwise).
-template <typename Cfg, bool V2> constexpr int zbuf_len()
-{
-    return V2 ? 2 * phase_units<Cfg>(0) : 1;
+    Red r;
+    r.q = sc.one_minus_rho * (INTERIOR ? (double)Cfg::ST * rd.dsq : rd.dsq) + sc.rho * rd.edge;
+    r.sse = rd.sse;
+    r.rsum = rd.rsum;
+    return r;
 }
 
 // XCD-aware tile order: the hardware hands block b to XCD b mod 8, so give
@@ -885,91 +1193,208 @@ __device__ __forceinline__ int xcd_tile(int b, int nb)
     return x * per + min(x, rem) + (b >> 3);
 }
 
-// Stage the tile whose top-left interior site is (r0, c0), with its halo,
-// into LDS, in two steps so that other work can run while the loads are in
-// flight: lattice_load issues every load of the thread (cells outside the
-// lattice become 0, their loads using an address clamped into the lattice,
-// which the site update relies on), lattice_store writes them to LDS.
-template <typename Cfg> constexpr int tile_loads()
+// The scalars of a sweep's site updates from the state it runs with.
+template <typename Real, int ST, bool B0>
+__device__ __forceinline__ SiteCtx<Real> site_ctx(const SweepArgs &a, const HyperIn &in,
+                                                  const Real *qtab)
 {
-    return (Cfg::LH * Cfg::LW + Cfg::NT - 1) / Cfg::NT;
+    SiteCtx<Real> sc;
+    sc.tau = uniform_value((Real)in.tau);
+    sc.lam = uniform_value((Real)in.lam);
+    sc.tau_rho = uniform_value((Real)(in.tau * a.rho));
+    site_scales<Real>(sc.tau, sc.lam, ST, sc.inv_q_full, sc.isd_full);
+    sc.inv_q_full = uniform_value(sc.inv_q_full);
+    sc.isd_full = uniform_value(sc.isd_full);
+    sc.beta0 = B0 ? uniform_value(in.beta0) : 0.0;
+    sc.beta0_r = B0 ? uniform_value((Real)in.beta0) : (Real)0;
+    sc.one_minus_rho = a.one_minus_rho;
+    sc.rho = a.rho;
+    sc.qtab = qtab;
+    return sc;
 }
 
-template <typename Real, typename Cfg>
-__device__ __forceinline__ void lattice_load(Real (&v)[tile_loads<Cfg>()],
-                                             const Real *__restrict__ src, int r0, int c0,
-                                             int rows, int cols)
+// The accumulator updates of a sweep: the history slots [lo, pending) and,
+// if own, the sweep's field (none unless the sweep ends its group).
+struct AccRange {
+    int lo, pending;
+    bool own;
+    __device__ __forceinline__ AccRange(const AccPlan &plan, unsigned t, long long burn_in)
+    {
+        pending = plan.pending;
+        own = pending >= 0 && (long long)t >= burn_in;
+        const long long first = burn_in - ((long long)t - pending);
+        lo = first > 0 ? (first < pending ? (int)first : pending) : 0;
+    }
+};
+
+// Write the thread's quads to dst and update the accumulators.  The
+// accumulated image is beta0 + x (x alone without an intercept).
+template <typename Real, typename Cfg, bool INTERIOR, bool B0>
+__device__ __forceinline__ void write_quads(const Real (&x)[Cfg::NQ][4], Real *__restrict__ dst,
+                                            const LatArgs<Real> &la, const SweepArgs &a,
+                                            const AccRange &acc, const TileAt &at, double beta0)
 {
-    constexpr int H = Cfg::H, LW = Cfg::LW, NT = Cfg::NT;
+    using D = Pair<double>::Mem;
+    using P = typename Pair<Real>::Mem;
+    constexpr int H = kHist<Real>;
+    const size_t n = (size_t)at.rows * at.cols;
+    double b0[H];
 #pragma unroll
-    for (int k = 0; k < tile_loads<Cfg>(); ++k) {
-        const int idx = (int)threadIdx.x + k * NT;
-        const int lr = idx / LW, lc = idx - (idx / LW) * LW;
-        const int r = r0 - H + lr, c = c0 - H + lc;
-        const int rc = min(max(r, 0), rows - 1), cc = min(max(c, 0), cols - 1);
-        v[k] = src[(size_t)rc * cols + cc];
-        if (r != rc || c != cc)
-            v[k] = (Real)0;
+    for (int k = 0; k < H; ++k)
+        b0[k] = B0 && acc.own && k >= acc.lo && k < acc.pending ? a.st->deferred_b0[k] : 0.0;
+    const int tid = thread_again<Cfg>();
+    if constexpr (INTERIOR) {
+        constexpr int R = 2 * Cfg::NQ;      // quad rows of the thread
+        constexpr int G = 2;                // of them in flight together: four spill, and a
+                                            // 2048 x 2048 sweep takes 35.9 instead of 32.8 us
+        constexpr unsigned W = sizeof(double) / sizeof(Real);
+        Real *const d0 = dst + at.first();
+        double *const p1 = a.s1 + at.first(), *const p2 = a.s2 + at.first();
+#pragma unroll
+        for (int g0 = 0; g0 < R; g0 += G) {
+            unsigned off[G];
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                const int h = g0 + j;
+                off[j] = quad_offset<Real, Cfg>(tid, h >> 1, at) + (h & 1) * at.row_bytes<Real>();
+                store_pair<Real>(at_bytes(d0, off[j]),
+                                 P{x[h >> 1][2 * (h & 1)], x[h >> 1][2 * (h & 1) + 1]});
+            }
+            if (!acc.own)
+                continue;
+            D v1[G], v2[G];
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                v1[j] = load_pair<double>(at_bytes(p1, W * off[j]));
+                v2[j] = load_pair<double>(at_bytes(p2, W * off[j]));
+            }
+            auto add = [&](int j, double u, double v) {
+                v1[j] = D{v1[j].x + u, v1[j].y + v};
+                v2[j] = D{v2[j].x + u * u, v2[j].y + v * v};
+            };
+#pragma unroll
+            for (int k = 0; k < H; ++k)
+                if (k >= acc.lo && k < acc.pending) {
+                    const Real *const f0 = la.hist + (k * n + at.first());
+                    P f[G];
+#pragma unroll
+                    for (int j = 0; j < G; ++j)
+                        f[j] = load_pair<Real>(at_bytes(f0, off[j]));
+#pragma unroll
+                    for (int j = 0; j < G; ++j)
+                        add(j, B0 ? (double)f[j].x + b0[k] : (double)f[j].x,
+                            B0 ? (double)f[j].y + b0[k] : (double)f[j].y);
+                }
+#pragma unroll
+            for (int j = 0; j < G; ++j) {
+                const Real u = x[(g0 + j) >> 1][2 * (j & 1)], v = x[(g0 + j) >> 1][2 * (j & 1) + 1];
+                add(j, B0 ? (double)u + beta0 : (double)u, B0 ? (double)v + beta0 : (double)v);
+                store_pair<double>(at_bytes(p1, W * off[j]), v1[j]);
+                store_pair<double>(at_bytes(p2, W * off[j]), v2[j]);
+            }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < Cfg::NQ; ++i) {
+            const int r = at.r0 + quad_row<Cfg>(tid, i), c = at.c0 + quad_col<Cfg>(tid);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                if (r + (s >> 1) < at.rows && c + (s & 1) < at.cols) {
+                    const size_t g = (size_t)(r + (s >> 1)) * at.cols + c + (s & 1);
+                    dst[g] = x[i][s];
+                    if (acc.own) {
+                        double v1 = a.s1[g], v2 = a.s2[g];
+                        for (int k = acc.lo; k < acc.pending; ++k) {
+                            const double f = (double)la.hist[k * n + g];
+                            const double u = B0 ? f + a.st->deferred_b0[k] : f;
+                            v1 = v1 + u;
+                            v2 = v2 + u * u;
+                        }
+                        const double u = B0 ? (double)x[i][s] + beta0 : (double)x[i][s];
+                        a.s1[g] = v1 + u;
+                        a.s2[g] = v2 + u * u;
+                    }
+                }
+            }
+        }
     }
 }
 
-template <typename Real, typename Cfg>
-__device__ __forceinline__ void lattice_store(Real *xs, const Real (&v)[tile_loads<Cfg>()])
+// Staging, phases, write-back and partials of one tile (INTERIOR: tile and
+// halo inside the lattice; the general path also takes tiles cut by its edge).
+template <typename Real, typename Cfg, bool INTERIOR, bool B0, bool V2>
+__device__ __forceinline__ void lattice_tile(Real *xs, const LatArgs<Real> &la, const SweepArgs &a,
+                                             const TileAt &at, const SiteCtx<Real> &sc,
+                                             const unsigned t, const int tile, const int rel,
+                                             const AccPlan &plan)
 {
-    constexpr int NL = tile_loads<Cfg>(), NT = Cfg::NT;
-#pragma unroll
-    for (int k = 0; k < NL; ++k) {
-        const int idx = (int)threadIdx.x + k * NT;
-        if (k < NL - 1 || idx < Cfg::LH * Cfg::LW)
-            xs[idx] = v[k];
+    const size_t n = (size_t)la.rows * la.cols;
+    const Real *src = plan.in >= 0 ? la.hist + plan.in * n : (t & 1u) ? la.x1 : la.x0;
+    QuadRegs<Real, Cfg> q;
+    {
+        Real ring[Cfg::NRL];
+        tile_load<Real, Cfg, INTERIOR>(q, ring, src, la.y, at);
+        if constexpr (kDrawAhead<Cfg> > 0)
+            draw_normals<Real, Cfg, 0, INTERIOR, V2, true>(q, at, a, t);
+        if constexpr (kDrawAhead<Cfg> > 1)
+            draw_normals<Real, Cfg, 1, INTERIOR, V2, true>(q, at, a, t);
+        if constexpr (kDrawAhead<Cfg> > 2)
+            draw_normals<Real, Cfg, 2, INTERIOR, V2, true>(q, at, a, t);
+        if constexpr (kDrawAhead<Cfg> > 3)
+            draw_normals<Real, Cfg, 3, INTERIOR, V2, true>(q, at, a, t);
+        stage_tile<Real, Cfg>(xs, q, ring);
     }
+    lds_barrier();
+    const Red rd = lattice_phases<Real, Cfg, INTERIOR, B0, true>(xs, q, at, sc, [&](auto J) {
+        constexpr int j = decltype(J)::value;
+        if constexpr (!kYAhead<Real, Cfg>) {
+            load_color<Real, Cfg, j, INTERIOR>(q.y, la.y, at);
+            if constexpr (Cfg::halo(j) > 0)
+                if ((int)threadIdx.x < Cfg::halo(j))
+                    q.yh[j] = load_halo_y<Real, Cfg, INTERIOR>(la.y, j, at);
+        }
+        if constexpr (j >= kDrawAhead<Cfg>)
+            draw_normals<Real, Cfg, j, INTERIOR, V2, true>(q, at, a, t);
+    });
+    Real *dst = plan.out >= 0 ? la.hist + plan.out * n : (t & 1u) ? la.x0 : la.x1;
+    write_quads<Real, Cfg, INTERIOR, B0>(q.x, dst, la, a, AccRange(plan, t, a.burn_in), at,
+                                         sc.beta0);
+    write_partials<Cfg::NT>(partials_of(a, rel), rd, tile);
 }
-
-// Tiles of a lattice take one of two compiled paths, an interior one (tile
-// and halo inside the lattice: compile-time neighbour flags and scales) and
-// the general one, or the general one alone.  The second halves the
-// kernel's code, which on this target decides more than the per-site
-// arithmetic once the code outgrows the instruction cache.
-#ifndef GMRF_LAT_SPLIT
-#define GMRF_LAT_SPLIT 1
-#endif
 
 // B0: the chain has an intercept (compile time, so that chains without one
 // run code with no trace of it).  rel: the sweep's index within its call
 // (sweep t = committed count + rel).  fold: the sweep before it in the call
 // has not been ended: every block ends it first (sums its partials and draws
 // tau, lam, beta0, identically in every block; the tile loads wait, since
-// holding them across the draws would cost the kernel its occupancy), and
-// the block of tile 0 records the draws for the next sweep kernel and the
-// commit.  Without fold the sweep runs with the committed
-// state (the first sweep of a call, and timing runs).  V2: the chain draws
-// its site normals by the paired contract (lattice_normals).
+// every load of the fold's chain would otherwise wait for them too: 2048 x
+// 2048 FP32 40.5 instead of 32.5 us), and the block of tile 0 records the
+// draws for the next sweep kernel and the commit.  Without fold the sweep
+// runs with the committed state (the first sweep of a call, and timing runs).
+// V2: the chain draws its site normals by the paired contract
+// (lattice_normal).
+//
+// What bounds it: at 2048 x 2048 neither memory (86 MB per FP32 sweep, ~2.7
+// TB/s) nor the vector units (56% of their issue slots, against 76% of 38%
+// more instructions before the quads) but the chain of fold, loads, phases
+// and write-back that every resident block walks through together; larger
+// lattices overlap the chains of successive blocks (4096 x 4096 FP32: 100 us,
+// 0.6 of the 2048 x 2048 time per site).
 template <typename Real, typename Cfg, bool B0, bool V2>
 __device__ __forceinline__ void lattice_sweep_block(const LatArgs<Real> &la, const SweepArgs &a,
-                                                    const int tile, const int rel, const int fold)
+                                                    const int tile, const int rel, const int fold,
+                                                    const AccPlan plan)
 {
-    constexpr int H = Cfg::H, LH = Cfg::LH, LW = Cfg::LW, NT = Cfg::NT;
-    constexpr int TH = Cfg::TH, TW = Cfg::TW;
-    constexpr int NPT = (TH * TW + NT - 1) / NT;       // interior sites per thread
-    constexpr int CH = Cfg::CH < NPT ? Cfg::CH : NPT;  // accumulator batch
-    __shared__ Real xs[LH * LW];
+    __shared__ __align__(16) Real xs[Cfg::LH * Cfg::LW];
     __shared__ Real qtab[2 * (Cfg::ST + 1)];
-    __shared__ Real zb[zbuf_len<Cfg, V2>()];
 
     const unsigned t = (unsigned)(a.st->sweep + (unsigned long long)rel);
-    const Real *src = (t & 1u) ? la.x1 : la.x0;
-    Real *dst = (t & 1u) ? la.x0 : la.x1;
-    const int rows = la.rows, cols = la.cols;
-    const int tr = tile / la.tiles_c, tc = tile - tr * la.tiles_c;
-    const int r0 = tr * TH, c0 = tc * TW;
-    const bool acc = (long long)t >= a.burn_in;
-
     HyperIn hin;
     if (fold) {
         SweepArgs fa = a;
         fa.dry = a.dry || tile != 0;      // one block stores the reductions and the trace
-        hin = end_sweep_block<NT>(fa, partials_of(a, rel - 1), t - 1u, inputs_of(a, rel - 1),
-                                  false);
+        hin = end_sweep_block<Cfg::NT>(fa, partials_of(a, rel - 1), t - 1u, inputs_of(a, rel - 1),
+                                       false);
         if (!fa.dry && threadIdx.x == 0) {
             double *const h = a.st->hs[rel & 1];
             h[0] = hin.tau;
@@ -979,166 +1404,85 @@ __device__ __forceinline__ void lattice_sweep_block(const LatArgs<Real> &la, con
     } else {
         hin = inputs_of(a, 0);
     }
-    Real v[tile_loads<Cfg>()];
-    lattice_load<Real, Cfg>(v, src, r0, c0, rows, cols);
-
-    SiteCtx<Real> sc;
-    sc.tau = (Real)hin.tau;
-    sc.lam = (Real)hin.lam;
-    sc.tau_rho = (Real)(hin.tau * a.rho);
-    site_scales<Real>(sc.tau, sc.lam, Cfg::ST, sc.inv_q_full, sc.isd_full);
-    sc.beta0 = B0 ? hin.beta0 : 0.0;
-    sc.beta0_r = (Real)sc.beta0;
-    sc.one_minus_rho = 1.0 - a.rho;
-    sc.rho = a.rho;
-    sc.t = t;
-    sc.seed = a.seed;
-    sc.instance = a.instance;
-    sc.qtab = qtab;
-    // phase 0's paired normals while the tile loads are in flight
-    if constexpr (V2)
-        lattice_normals<Real, Cfg, 0>(zb, r0, c0, rows, cols, sc);
-
-    lattice_store<Real, Cfg>(xs, v);
+    if (B0 && plan.out >= 0 && tile == 0 && threadIdx.x == 0 && !a.dry)
+        a.st->deferred_b0[plan.out] = hin.beta0;
+    const SiteCtx<Real> sc = site_ctx<Real, Cfg::ST, B0>(a, hin, qtab);
     qtab_fill<Real, Cfg::ST>(qtab, sc.tau, sc.lam);
-    lds_barrier();
-
-    Red rd;
-#if GMRF_LAT_SPLIT
-    const bool interior = r0 >= H && c0 >= H && r0 + TH + Cfg::HH <= rows &&
-                          c0 + TW + Cfg::HH <= cols;
-    if (interior)
-        lattice_phases<Real, Cfg, true, B0, V2>(xs, la.y, r0, c0, rows, cols, sc, rd, zb);
+    const int tr = tile / la.tiles_c, tc = tile - tr * la.tiles_c;
+    const TileAt at{tr * Cfg::TH, tc * Cfg::TW, la.rows, la.cols};
+    const int interior = at.r0 >= Cfg::RB && at.c0 >= Cfg::CB &&
+                         at.r0 + Cfg::TH + Cfg::RA <= at.rows &&
+                         at.c0 + Cfg::TW + Cfg::CA <= at.cols && at.cols <= kOffsetCols;
+    // two paths to the end, so that neither's registers live across the other
+    if (__builtin_amdgcn_readfirstlane(interior))
+        lattice_tile<Real, Cfg, true, B0, V2>(xs, la, a, at, sc, t, tile, rel, plan);
     else
-#endif
-        lattice_phases<Real, Cfg, false, B0, V2>(xs, la.y, r0, c0, rows, cols, sc, rd, zb);
-
-    // Write the interior back and update the accumulators, CH sites per
-    // thread per batch so their loads are in flight together.
-#pragma unroll
-    for (int k0 = 0; k0 < NPT; k0 += CH) {
-        double o1[CH], o2[CH];
-        size_t g[CH];
-        bool ok[CH];
-#pragma unroll
-        for (int j = 0; j < CH; ++j) {
-            const int idx = (int)threadIdx.x + (k0 + j) * NT;
-            const int r = r0 + idx / TW, c = c0 + idx % TW;
-            ok[j] = (k0 + j < NPT) && idx < TH * TW && r < rows && c < cols;
-            g[j] = (size_t)min(r, rows - 1) * cols + min(c, cols - 1);
-            o1[j] = 0.0;
-            o2[j] = 0.0;
-            if (acc) {
-                o1[j] = a.s1[g[j]];
-                o2[j] = a.s2[g[j]];
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < CH; ++j) {
-            if (ok[j]) {
-                const int idx = (int)threadIdx.x + (k0 + j) * NT;
-                const Real v = xs[(idx / TW + H) * LW + idx % TW + H];
-                dst[g[j]] = v;
-                if (acc) {
-                    // the accumulated image is beta0 + x (x alone without an intercept)
-                    const double dv = B0 ? (double)v + sc.beta0 : (double)v;
-                    a.s1[g[j]] = o1[j] + dv;
-                    a.s2[g[j]] = o2[j] + dv * dv;
-                }
-            }
-        }
-    }
-    write_partials<NT>(partials_of(a, rel), rd, tile);
+        lattice_tile<Real, Cfg, false, B0, V2>(xs, la, a, at, sc, t, tile, rel, plan);
 }
 
 template <typename Real, typename Cfg, bool B0, bool V2>
-__global__ __launch_bounds__(Cfg::NT) void lattice_sweep_kernel(LatArgs<Real> la, SweepArgs a,
-                                                                int rel, int fold)
+__global__ __launch_bounds__(Cfg::NT, (kLatWaves<Real, Cfg>)) void lattice_sweep_kernel(LatArgs<Real> la, SweepArgs a,
+                                                                int rel, int fold, AccPlan plan)
 {
     lattice_sweep_block<Real, Cfg, B0, V2>(la, a, xcd_tile((int)blockIdx.x, (int)gridDim.x), rel,
-                                           fold);
+                                           fold, plan);
 }
 
 // A lattice that fits one tile, many sweeps in one launch (one block): the
 // field stays in LDS (after a sweep every site of the tile is final, so the
-// next sweep needs no reload), this thread's accumulators stay in registers,
-// and the end-of-sweep reductions and draws run in the block itself.  Every
-// operation is the one the tile kernel and the end of its sweep perform for a
-// single-tile lattice, in the same order, so the results are bitwise those of
-// tile shape 0.  With a.dry set (timing) it writes only the state buffer that
-// the sweep after the last one would overwrite.
+// next sweep needs no reload), this thread's x, y and accumulators stay in
+// registers, and the end-of-sweep reductions and draws run in the block
+// itself.  Every operation is the one the tile kernel and the end of its
+// sweep perform for a single-tile lattice, in the same order, so the results
+// are bitwise those of tile shape 0.  With a.dry set (timing) it writes only
+// the state buffer that the sweep after the last one would overwrite.
 template <typename Real, typename Cfg, bool B0, bool V2>
 __global__ __launch_bounds__(Cfg::NT) void lattice_persistent_kernel(LatArgs<Real> la, SweepArgs a,
                                                                      int nsweeps)
 {
-    constexpr int H = Cfg::H, LH = Cfg::LH, LW = Cfg::LW, NT = Cfg::NT;
-    constexpr int TH = Cfg::TH, TW = Cfg::TW;
-    constexpr int NPT = (TH * TW + NT - 1) / NT;
-    __shared__ Real xs[LH * LW];
+    constexpr int NT = Cfg::NT, NQ = Cfg::NQ;
+    __shared__ __align__(16) Real xs[Cfg::LH * Cfg::LW];
     __shared__ Real qtab[2 * (Cfg::ST + 1)];
     __shared__ double red[kPartials * (NT / 64)];
     __shared__ double hyp[3];
     __shared__ UnitDraws ub[kUnitBatch][2];
-    __shared__ Real zb[zbuf_len<Cfg, V2>()];
-    const int rows = la.rows, cols = la.cols;
+    const TileAt at{0, 0, la.rows, la.cols};
     const int lane = (int)threadIdx.x & 63;
     unsigned t = (unsigned)a.st->sweep;
     long long nacc = a.st->n_acc;
-    double tau = a.st->tau, lam = a.st->lam, b0 = B0 ? a.st->beta0 : 0.0;
-    {
-        Real v[tile_loads<Cfg>()];
-        lattice_load<Real, Cfg>(v, (t & 1u) ? la.x1 : la.x0, 0, 0, rows, cols);
-        lattice_store<Real, Cfg>(xs, v);
-    }
-    double s1r[NPT], s2r[NPT];
-    int gi[NPT];
-    bool own[NPT];
-#pragma unroll
-    for (int k = 0; k < NPT; ++k) {
-        const int idx = (int)threadIdx.x + k * NT;
-        const int r = idx / TW, c = idx % TW;
-        own[k] = idx < TH * TW && r < rows && c < cols;
-        gi[k] = min(r, rows - 1) * cols + min(c, cols - 1);
-        s1r[k] = a.s1[gi[k]];
-        s2r[k] = a.s2[gi[k]];
-    }
-    bool accumulated = false;
+    HyperIn in{a.st->tau, a.st->lam, B0 ? a.st->beta0 : 0.0};
+    QuadRegs<Real, Cfg> q;
+    double s1r[NQ][4], s2r[NQ][4];
+    load_quads<Real, Cfg, false>(q.x, (t & 1u) ? la.x1 : la.x0, at);
+    load_quads<Real, Cfg, false>(q.y, la.y, at);
+    load_quads<double, Cfg, false>(s1r, a.s1, at);
+    load_quads<double, Cfg, false>(s2r, a.s2, at);
+    // the ring lies outside the lattice: 0
+    for (int i = (int)threadIdx.x; i < Cfg::LH * Cfg::LW; i += NT)
+        xs[i] = (Real)0;
     lds_barrier();
+    stage_quads<Real, Cfg>(xs, q.x);
+    bool accumulated = false;
     for (int s = 0; s < nsweeps; ++s) {
         if (s % kUnitBatch == 0) {
             unit_draw_batch<NT>(a, t, min(kUnitBatch, nsweeps - s), ub);
             lds_barrier();
         }
-        SiteCtx<Real> sc;
-        sc.tau = (Real)tau;
-        sc.lam = (Real)lam;
-        sc.tau_rho = (Real)(tau * a.rho);
-        site_scales<Real>(sc.tau, sc.lam, Cfg::ST, sc.inv_q_full, sc.isd_full);
-        sc.beta0 = b0;
-        sc.beta0_r = (Real)sc.beta0;
-        sc.one_minus_rho = 1.0 - a.rho;
-        sc.rho = a.rho;
-        sc.t = t;
-        sc.seed = a.seed;
-        sc.instance = a.instance;
-        sc.qtab = qtab;
+        const SiteCtx<Real> sc = site_ctx<Real, Cfg::ST, B0>(a, in, qtab);
         qtab_fill<Real, Cfg::ST>(qtab, sc.tau, sc.lam);
-        if constexpr (V2)
-            lattice_normals<Real, Cfg, 0>(zb, 0, 0, rows, cols, sc);
         lds_barrier();
-        Red rd;
-        lattice_phases<Real, Cfg, false, B0, V2>(xs, la.y, 0, 0, rows, cols, sc, rd, zb);
+        Red rd = lattice_phases<Real, Cfg, false, B0, false>(xs, q, at, sc, [&](auto J) {
+            draw_normals<Real, Cfg, decltype(J)::value, false, V2, false>(q, at, a, t);
+        });
         if ((long long)t >= a.burn_in) {
 #pragma unroll
-            for (int k = 0; k < NPT; ++k) {
-                if (own[k]) {
-                    const int idx = (int)threadIdx.x + k * NT;
-                    const Real v = xs[(idx / TW + H) * LW + idx % TW + H];
-                    const double dv = B0 ? (double)v + sc.beta0 : (double)v;
-                    s1r[k] = s1r[k] + dv;
-                    s2r[k] = s2r[k] + dv * dv;
+            for (int i = 0; i < NQ; ++i)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const double dv = B0 ? (double)q.x[i][k] + sc.beta0 : (double)q.x[i][k];
+                    s1r[i][k] = s1r[i][k] + dv;
+                    s2r[i][k] = s2r[i][k] + dv * dv;
                 }
-            }
             ++nacc;
             accumulated = true;
         }
@@ -1148,7 +1492,7 @@ __global__ __launch_bounds__(Cfg::NT) void lattice_persistent_kernel(LatArgs<Rea
             rd.q = __shfl(rd.q, 0, 64);
             rd.sse = __shfl(rd.sse, 0, 64);
             rd.rsum = __shfl(rd.rsum, 0, 64);
-            const HyperIn out = end_of_sweep_draws(a, t, rd, HyperIn{tau, lam, b0}, lane,
+            const HyperIn out = end_of_sweep_draws(a, t, rd, in, lane,
                                                    ub[s % kUnitBatch][lane < 2 ? lane : 0]);
             if (lane == 0) {
                 hyp[0] = out.tau;
@@ -1157,22 +1501,26 @@ __global__ __launch_bounds__(Cfg::NT) void lattice_persistent_kernel(LatArgs<Rea
             }
         }
         lds_barrier();
-        tau = hyp[0];
-        lam = hyp[1];
-        b0 = hyp[2];
+        in = HyperIn{hyp[0], hyp[1], hyp[2]};
         ++t;
     }
     // the state after the last sweep: x in buffer t mod 2, the accumulators,
     // the counters (the draws already stored tau, lam, beta0 and reductions)
     Real *dst = (t & 1u) ? la.x1 : la.x0;
+    const int tid = (int)threadIdx.x;
 #pragma unroll
-    for (int k = 0; k < NPT; ++k) {
-        if (own[k]) {
-            const int idx = (int)threadIdx.x + k * NT;
-            dst[gi[k]] = xs[(idx / TW + H) * LW + idx % TW + H];
-            if (accumulated && !a.dry) {
-                a.s1[gi[k]] = s1r[k];
-                a.s2[gi[k]] = s2r[k];
+    for (int i = 0; i < NQ; ++i) {
+        const int r = quad_row<Cfg>(tid, i), c = quad_col<Cfg>(tid);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int rr = r + (k >> 1), cc = c + (k & 1);
+            if (rr < at.rows && cc < at.cols) {
+                const int g = rr * at.cols + cc;
+                dst[g] = q.x[i][k];
+                if (accumulated && !a.dry) {
+                    a.s1[g] = s1r[i][k];
+                    a.s2[g] = s2r[i][k];
+                }
             }
         }
     }
@@ -1196,15 +1544,16 @@ struct LatTile {
 // with_hyper: this call's GMRF_WITH_HYPER (the job tables are built once);
 // rel, fold: as for lattice_sweep_block, the same for every chain.
 template <typename Real, typename Cfg, bool B0>
-__global__ __launch_bounds__(Cfg::NT) void lattice_batch_kernel(const LatJob<Real> *jobs,
+__global__ __launch_bounds__(Cfg::NT, (kLatWaves<Real, Cfg>)) void lattice_batch_kernel(const LatJob<Real> *jobs,
                                                                 const LatTile *tiles,
-                                                                int with_hyper, int rel, int fold)
+                                                                int with_hyper, int rel, int fold,
+                                                                AccPlan plan)
 {
     const LatTile tl = tiles[xcd_tile((int)blockIdx.x, (int)gridDim.x)];
     const LatJob<Real> &j = jobs[tl.job];
     SweepArgs a = j.a;
     a.with_hyper = with_hyper;
-    lattice_sweep_block<Real, Cfg, B0, false>(j.la, a, tl.tile, rel, fold);
+    lattice_sweep_block<Real, Cfg, B0, false>(j.la, a, tl.tile, rel, fold, plan);
 }
 
 // ---------------------------------------------------------------------------
@@ -2132,7 +2481,7 @@ constexpr TileShape kTiles[GMRF_NUM_TILES] = {{64, 64, 512}, {32, 32, 256}, {64,
 constexpr int kPersistent = 2;
 constexpr int kFused = 1;          // general graphs: the chunked one-launch sweep
 template <int ST, int K>
-using LatticeCfg = LatCfg<ST, kTiles[K].th, kTiles[K].tw, kTiles[K].nt, 4>;
+using LatticeCfg = LatCfg<ST, kTiles[K].th, kTiles[K].tw, kTiles[K].nt>;
 static_assert(GMRF_NUM_TILES == 3, "tile dispatch below covers three shapes");
 
 // Tile configuration (0 or 1) whose kernels sweep a chain of shape k.
@@ -2287,6 +2636,7 @@ SweepArgs make_args(const gmrf_chain *c, unsigned flags)
     a.b_tau = c->model.b_tau;
     a.b_lam = c->model.b_lam;
     a.rho = c->g->h.rho;
+    a.one_minus_rho = 1.0 - a.rho;
     a.burn_in = (long long)c->model.burn_in;
     a.seed = c->seed;
     a.instance = c->instance;
@@ -2314,8 +2664,18 @@ template <typename Real> LatArgs<Real> lattice_args(const gmrf_chain *c, int sha
     la.rows = h.rows;
     la.cols = h.cols;
     la.tiles_c = (h.cols + kTiles[shape].tw - 1) / kTiles[shape].tw;
+    la.hist = reinterpret_cast<Real *>(c->d_stats);
     return la;
 }
+
+// Place of relative sweep i of a call of nsweeps in its group of G sweeps.
+AccPlan acc_plan(int i, int nsweeps, int G)
+{
+    const int g = i % G;
+    const bool last = g == G - 1 || i == nsweeps - 1;
+    return AccPlan{g - 1, last ? -1 : g, last ? g : -1};
+}
+template <typename Real> constexpr int kGroup = 1 + kHist<Real>;
 
 template <typename Real> CsrArgs<Real> csr_args(const gmrf_chain *c)
 {
@@ -2338,7 +2698,7 @@ template <typename Real> CsrArgs<Real> csr_args(const gmrf_chain *c)
 // the end of the sweep kernel(s), for the profiling entry point.
 template <typename Real, int ST, int K>
 void launch_lattice_shape(const gmrf_chain *c, const SweepArgs &a, hipStream_t s, hipEvent_t ev0,
-                          hipEvent_t ev1, int rel, int fold)
+                          hipEvent_t ev1, int rel, int fold, const AccPlan &plan)
 {
     const LatArgs<Real> la = lattice_args<Real>(c);
     using Cfg = LatticeCfg<ST, K>;
@@ -2350,19 +2710,23 @@ void launch_lattice_shape(const gmrf_chain *c, const SweepArgs &a, hipStream_t s
                           : lattice_sweep_kernel<Real, Cfg, false, false>);
     if (ev0 || ev1)
         hipExtLaunchKernelGGL(kern, dim3(c->total_slots), dim3(Cfg::NT), 0, s, ev0, ev1, 0, la,
-                              a, rel, fold);
+                              a, rel, fold, plan);
     else
-        hipLaunchKernelGGL(kern, dim3(c->total_slots), dim3(Cfg::NT), 0, s, la, a, rel, fold);
+        hipLaunchKernelGGL(kern, dim3(c->total_slots), dim3(Cfg::NT), 0, s, la, a, rel, fold,
+                           plan);
 }
 
 template <typename Real, int ST>
 void launch_lattice(const gmrf_chain *c, const SweepArgs &a, hipStream_t s, hipEvent_t ev0,
-                    hipEvent_t ev1, int rel, int fold)
+                    hipEvent_t ev1, int rel, int fold, int i, int nsweeps)
 {
+    AccPlan plan = acc_plan(i, nsweeps, kGroup<Real>);
+    if (a.dry)
+        plan.in = -1;       // timing runs read the current field
     if (tile_cfg(c->lat_tile) == 0)
-        launch_lattice_shape<Real, ST, 0>(c, a, s, ev0, ev1, rel, fold);
+        launch_lattice_shape<Real, ST, 0>(c, a, s, ev0, ev1, rel, fold, plan);
     else
-        launch_lattice_shape<Real, ST, 1>(c, a, s, ev0, ev1, rel, fold);
+        launch_lattice_shape<Real, ST, 1>(c, a, s, ev0, ev1, rel, fold, plan);
 }
 
 // nsweeps sweeps of a shape-2 chain in one launch of the persistent kernel.
@@ -2615,20 +2979,21 @@ void launch_csr(const gmrf_chain *c, const SweepArgs &a, hipStream_t s, hipEvent
 // graph: the color passes).  A timing run (a.dry) repeats relative sweep 0:
 // it never advances the sweep count, so every repetition reads the current
 // state buffer and writes only the other one.
-void launch_sweep_kernels(const gmrf_chain *c, const SweepArgs &a, hipStream_t s, int rel,
-                          hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr)
+void launch_sweep_kernels(const gmrf_chain *c, const SweepArgs &a, hipStream_t s, int i,
+                          int nsweeps, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr)
 {
     const bool f64 = c->prec == GMRF_FP64;
+    int rel = i;
     if (a.dry || !a.deferred)   // every sweep committed on its own: relative sweep 0
         rel = 0;
     const int fold = rel > 0 ? 1 : 0;
     if (is_lattice(c->g)) {
         if (c->g->h.stencil == 4)
-            f64 ? launch_lattice<double, 4>(c, a, s, ev0, ev1, rel, fold)
-                : launch_lattice<float, 4>(c, a, s, ev0, ev1, rel, fold);
+            f64 ? launch_lattice<double, 4>(c, a, s, ev0, ev1, rel, fold, i, nsweeps)
+                : launch_lattice<float, 4>(c, a, s, ev0, ev1, rel, fold, i, nsweeps);
         else
-            f64 ? launch_lattice<double, 8>(c, a, s, ev0, ev1, rel, fold)
-                : launch_lattice<float, 8>(c, a, s, ev0, ev1, rel, fold);
+            f64 ? launch_lattice<double, 8>(c, a, s, ev0, ev1, rel, fold, i, nsweeps)
+                : launch_lattice<float, 8>(c, a, s, ev0, ev1, rel, fold, i, nsweeps);
     } else {
         f64 ? launch_csr<double>(c, a, s, ev0, ev1, rel, fold)
             : launch_csr<float>(c, a, s, ev0, ev1, rel, fold);
@@ -2672,7 +3037,7 @@ void launch_sweeps(const gmrf_chain *c, const SweepArgs &a, int nsweeps, hipStre
 {
     for (int i = 0; i < nsweeps; ++i) {
         launch_units_ahead(c, a, i, nsweeps, s);
-        launch_sweep_kernels(c, a, s, i);
+        launch_sweep_kernels(c, a, s, i, nsweeps);
         launch_commit_after(c, a, i, nsweeps, s);
     }
 }
@@ -2993,7 +3358,8 @@ int install_image(gmrf_batch *b, const BatchImage &im, hipStream_t stream)
 }
 
 template <typename Real, int ST, bool B0, int K>
-void launch_lattice_group(const gmrf_batch *b, int hyper, int rel, int fold, hipStream_t s)
+void launch_lattice_group(const gmrf_batch *b, int hyper, int rel, int fold, const AccPlan &plan,
+                          hipStream_t s)
 {
     const int w = (ST == 8 ? 1 : 0) + (B0 ? 2 : 0) + 4 * K;
     using Cfg = LatticeCfg<ST, K>;
@@ -3001,7 +3367,7 @@ void launch_lattice_group(const gmrf_batch *b, int hyper, int rel, int fold, hip
         hipLaunchKernelGGL((lattice_batch_kernel<Real, Cfg, B0>), dim3(b->lat_tile_count[w]),
                            dim3(Cfg::NT), 0, s,
                            static_cast<const LatJob<Real> *>(b->lat_jobs[w]), b->lat_tiles[w],
-                           hyper, rel, fold);
+                           hyper, rel, fold, plan);
 }
 
 template <typename Real, bool B0>
@@ -3021,16 +3387,16 @@ void launch_csr_group(const gmrf_batch *b, size_t col, int hyper, hipStream_t s)
 // previous one first).
 template <typename Real>
 void launch_batch_lattice_kernels(const gmrf_batch *b, int hyper, int rel, int fold,
-                                  hipStream_t s)
+                                  const AccPlan &plan, hipStream_t s)
 {
-    launch_lattice_group<Real, 4, false, 0>(b, hyper, rel, fold, s);
-    launch_lattice_group<Real, 8, false, 0>(b, hyper, rel, fold, s);
-    launch_lattice_group<Real, 4, true, 0>(b, hyper, rel, fold, s);
-    launch_lattice_group<Real, 8, true, 0>(b, hyper, rel, fold, s);
-    launch_lattice_group<Real, 4, false, 1>(b, hyper, rel, fold, s);
-    launch_lattice_group<Real, 8, false, 1>(b, hyper, rel, fold, s);
-    launch_lattice_group<Real, 4, true, 1>(b, hyper, rel, fold, s);
-    launch_lattice_group<Real, 8, true, 1>(b, hyper, rel, fold, s);
+    launch_lattice_group<Real, 4, false, 0>(b, hyper, rel, fold, plan, s);
+    launch_lattice_group<Real, 8, false, 0>(b, hyper, rel, fold, plan, s);
+    launch_lattice_group<Real, 4, true, 0>(b, hyper, rel, fold, plan, s);
+    launch_lattice_group<Real, 8, true, 0>(b, hyper, rel, fold, plan, s);
+    launch_lattice_group<Real, 4, false, 1>(b, hyper, rel, fold, plan, s);
+    launch_lattice_group<Real, 8, false, 1>(b, hyper, rel, fold, plan, s);
+    launch_lattice_group<Real, 4, true, 1>(b, hyper, rel, fold, plan, s);
+    launch_lattice_group<Real, 8, true, 1>(b, hyper, rel, fold, plan, s);
 }
 
 template <typename Real, bool B0>
@@ -3052,9 +3418,11 @@ void launch_fused_group(const gmrf_batch *b, int hyper, int rel, int fold, hipSt
 }
 
 template <typename Real>
-void launch_batch_sweep_kernels(const gmrf_batch *b, int hyper, int rel, int fold, hipStream_t s)
+void launch_batch_sweep_kernels(const gmrf_batch *b, int hyper, int rel, int fold, int nsweeps,
+                                hipStream_t s)
 {
-    launch_batch_lattice_kernels<Real>(b, hyper, rel, fold, s);
+    launch_batch_lattice_kernels<Real>(b, hyper, rel, fold, acc_plan(rel, nsweeps, kGroup<Real>),
+                                       s);
     launch_fused_group<Real, false>(b, hyper, rel, fold, s);
     launch_fused_group<Real, true>(b, hyper, rel, fold, s);
     // color c of every general-graph chain before color c + 1 of any
@@ -3078,9 +3446,9 @@ void launch_batch_sweeps(const gmrf_batch *b, int nsweeps, unsigned flags, hipSt
                                dim3(kUnitThreads), 0, s, b->unit_args, i,
                                std::min(kUnitBatch, nsweeps - i));
         if (b->prec == GMRF_FP64)
-            launch_batch_sweep_kernels<double>(b, hyper, i, i > 0 ? 1 : 0, s);
+            launch_batch_sweep_kernels<double>(b, hyper, i, i > 0 ? 1 : 0, nsweeps, s);
         else
-            launch_batch_sweep_kernels<float>(b, hyper, i, i > 0 ? 1 : 0, s);
+            launch_batch_sweep_kernels<float>(b, hyper, i, i > 0 ? 1 : 0, nsweeps, s);
         if (b->n_csr > 0)       // general graphs: every sweep ends in its own commit
             hipLaunchKernelGGL(commit_batch_kernel, dim3((unsigned)b->n_csr),
                                dim3(kFinishThreads), 0, s, b->csr_commit, 0, 1, hyper);
@@ -3658,7 +4026,7 @@ int gmrf_sweep_timed(gmrf_chain *c, int32_t nsweeps, uint32_t flags, hipStream_t
         hipError_t he = hipSuccess;
         for (int i = 0; i < nsweeps && he == hipSuccess; ++i) {
             launch_units_ahead(c, a, i, nsweeps, stream);
-            launch_sweep_kernels(c, a, stream, i, ev[2 * i], ev[2 * i + 1]);
+            launch_sweep_kernels(c, a, stream, i, nsweeps, ev[2 * i], ev[2 * i + 1]);
             launch_commit_after(c, a, i, nsweeps, stream);
             he = hipGetLastError();
         }
@@ -4126,8 +4494,11 @@ int gmrf_batch_autotune(gmrf_batch *b, int32_t reps, hipStream_t stream, int32_t
                 he = hipEventRecord(e0, stream);
             if (he == hipSuccess) {
                 // dry passes repeat relative sweep 0 (see launch_sweep_kernels)
-                b->prec == GMRF_FP64 ? launch_batch_lattice_kernels<double>(b, 1, 0, 0, stream)
-                                     : launch_batch_lattice_kernels<float>(b, 1, 0, 0, stream);
+                AccPlan plan = acc_plan(r, reps + 1, b->prec == GMRF_FP64 ? kGroup<double>
+                                                                         : kGroup<float>);
+                plan.in = -1;
+                b->prec == GMRF_FP64 ? launch_batch_lattice_kernels<double>(b, 1, 0, 0, plan, stream)
+                                     : launch_batch_lattice_kernels<float>(b, 1, 0, 0, plan, stream);
                 he = hipGetLastError();
             }
         }

@@ -20,6 +20,13 @@ struct Words4 {
     uint32_t w0, w1, w2, w3;
 };
 
+// a ^ b ^ c in one instruction (truth table 0x96 of gfx950's three-input
+// logic operation; the compiler emits two).
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c)
+{
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
 // Ten Philox rounds.  Each round multiplies two counter words by the Philox
 // multipliers, mixes the high halves with the other two words and the key,
 // and advances the key by the Weyl increments.
@@ -34,9 +41,9 @@ __device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32
         const uint64_t pb = (uint64_t)kMulB * c2;
         const uint32_t a_hi = (uint32_t)(pa >> 32), a_lo = (uint32_t)pa;
         const uint32_t b_hi = (uint32_t)(pb >> 32), b_lo = (uint32_t)pb;
-        c0 = b_hi ^ c1 ^ k0;
+        c0 = xor3(b_hi, c1, k0);
         c1 = b_lo;
-        c2 = a_hi ^ c3 ^ k1;
+        c2 = xor3(a_hi, c3, k1);
         c3 = a_lo;
         k0 += kIncA;
         k1 += kIncB;
@@ -231,24 +238,22 @@ __device__ __forceinline__ float normal_f32(const Words4 &w)
            __builtin_amdgcn_cosf(u2);
 }
 
-// Both Box-Muller normals of one block (the paired contract: the cosine
+// One branch of a block's Box-Muller pair (the paired contract: the cosine
 // branch for the lower-ranked site of a pair, the sine branch for its
-// partner); one logarithm and one square root serve the two.
-__device__ __forceinline__ void normal_pair_f64(const Words4 &w, double &zc, double &zs)
+// partner).
+__device__ __forceinline__ double normal_branch_f64(const Words4 &w, bool sine)
 {
-    const double r = sqrt_f64(-2.0 * log_open_unit(open_uniform_f64(w.w0, w.w1)));
-    zc = r * cos_2pi_words(w.w2, w.w3);
-    zs = r * sin_2pi_words(w.w2, w.w3);
+    return sqrt_f64(-2.0 * log_open_unit(open_uniform_f64(w.w0, w.w1))) *
+           cos_2pi_words(sine ? w.w2 - 0x40000000u : w.w2, w.w3);
 }
 
-__device__ __forceinline__ void normal_pair_f32(const Words4 &w, float &zc, float &zs)
+__device__ __forceinline__ float normal_branch_f32(const Words4 &w, bool sine)
 {
     const float u1 = fmaf((float)w.w0, 0x1p-32f, fmaf((float)(w.w1 >> 8), 0x1p-56f, 0x1p-57f));
     const float u2 = (float)w.w2 * 0x1p-32f;
     constexpr float kMinus2Ln2 = -1.38629436111989061883f;   // -2 ln 2
     const float r = __builtin_amdgcn_sqrtf(kMinus2Ln2 * __builtin_amdgcn_logf(u1));
-    zc = r * __builtin_amdgcn_cosf(u2);
-    zs = r * __builtin_amdgcn_sinf(u2);
+    return r * (sine ? __builtin_amdgcn_sinf(u2) : __builtin_amdgcn_cosf(u2));
 }
 
 template <typename Real> __device__ __forceinline__ Real site_normal(const Words4 &w);
@@ -262,16 +267,12 @@ template <> __device__ __forceinline__ float site_normal<float>(const Words4 &w)
 }
 
 template <typename Real>
-__device__ __forceinline__ void site_normal_pair(const Words4 &w, Real &zc, Real &zs);
-template <>
-__device__ __forceinline__ void site_normal_pair<double>(const Words4 &w, double &zc, double &zs)
+__device__ __forceinline__ Real site_normal_branch(const Words4 &w, bool sine)
 {
-    normal_pair_f64(w, zc, zs);
-}
-template <>
-__device__ __forceinline__ void site_normal_pair<float>(const Words4 &w, float &zc, float &zs)
-{
-    normal_pair_f32(w, zc, zs);
+    if constexpr (sizeof(Real) == 8)
+        return normal_branch_f64(w, sine);
+    else
+        return normal_branch_f32(w, sine);
 }
 
 constexpr int kGammaMaxAttempts = 64;
