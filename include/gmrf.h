@@ -257,7 +257,8 @@ int gmrf_chain_create_binomial(const gmrf_graph *g, const gmrf_model *m, const d
  * sweep of the call (sums its reductions and draws the hyperparameters, in
  * every block); a one-block commit kernel ends the call's last sweep.  A
  * general graph in shape 0 runs one kernel per color and the commit kernel
- * after every sweep; shape 2 runs the whole call in one launch.  With
+ * after every sweep; shape 2 runs the whole call in one launch (a lattice:
+ * 128 sweeps per launch, after one that draws their site normals).  With
  * GMRF_WITH_HYPER a small kernel
  * draws the rate-free parts of the hyperparameter draws (which depend only
  * on the sweep index) before every 128 sweeps.  Sec. 2.3, Algorithm 1; the
@@ -367,8 +368,8 @@ int gmrf_set_trace(gmrf_chain *c, double *d_trace, int64_t capacity, hipStream_t
  * lattice sweep run tile by tile): shape 0 is a 64 x 64 tile with 512
  * threads, shape 1 a 32 x 32 tile with 256 threads; shape 2 (lattices of at
  * most 64 x 64 sites) is shape 0's single tile swept by a persistent
- * one-block kernel that runs all the sweeps of a gmrf_sweep call, with their
- * draws, in one launch (bitwise the results of shape 0).  A new lattice chain
+ * one-block kernel that runs 128 sweeps of a gmrf_sweep call, with their
+ * draws, per launch (bitwise the results of shape 0).  A new lattice chain
  * starts with shape 2 if the lattice fits one 64 x 64 tile, else with shape 0
  * if that gives at least 512 tiles, else shape 1.  Shapes 0 and 1 group the
  * FP64 reductions differently (results agree to rounding, not bit for bit);

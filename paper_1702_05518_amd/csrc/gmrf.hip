@@ -125,12 +125,36 @@ constexpr int kPartials = 3;
 
 constexpr int kThreads = 256;   // CSR passes and stats kernels
 
-template <typename T> __device__ __forceinline__ T wave_sum(T v)
+// v of the lane that the DPP control names.
+template <int CTRL> __device__ __forceinline__ double dpp_lane(double v)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1)
-        v += __shfl_down(v, off, 64);
-    return v;
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, CTRL, 0xf, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Sum over the wavefront, in every lane (all 64 lanes active).  A butterfly
+// on register lanes: neighbours, pairs, the mirrored halves of 8 and of 16
+// lanes, then the 16-lane rows and the two halves exchanged.  The
+// shuffles through LDS that it replaces cost a round trip in each of the six
+// steps, twice in every sweep's chain (partials and fold): 509 x 517 FP32
+// 10.2 -> 9.5 us per sweep, 2048 x 2048 FP32 32.1 -> 31.2 us.
+__device__ __forceinline__ double wave_sum(double v)
+{
+    v += dpp_lane<0xB1>(v);      // quad_perm [1, 0, 3, 2]
+    v += dpp_lane<0x4E>(v);      // quad_perm [2, 3, 0, 1]
+    v += dpp_lane<0x141>(v);     // row_half_mirror
+    v += dpp_lane<0x140>(v);     // row_mirror
+    auto halves = [](double x, auto swap) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, x);
+        const auto lo = swap((uint32_t)b), hi = swap((uint32_t)(b >> 32));
+        return __builtin_bit_cast(double, ((uint64_t)hi[0] << 32) | lo[0]) +
+               __builtin_bit_cast(double, ((uint64_t)hi[1] << 32) | lo[1]);
+    };
+    v = halves(v, [](uint32_t w) { return __builtin_amdgcn_permlane16_swap(w, w, false, false); });
+    return halves(v,
+                  [](uint32_t w) { return __builtin_amdgcn_permlane32_swap(w, w, false, false); });
 }
 
 // Barrier that orders LDS only: global loads issued before it stay in flight
@@ -196,6 +220,17 @@ struct HyperIn {
     double tau, lam, beta0;
 };
 
+// Where the trace rows go (NULL: nowhere).  Read at run time, so that batches
+// and captured graphs see changes; a kernel of many sweeps reads it once.
+struct TraceTo {
+    double *rows;
+    long long cap;
+};
+__device__ __forceinline__ TraceTo trace_of(const SweepArgs &a)
+{
+    return TraceTo{a.st->trace, a.st->trace_cap};
+}
+
 __device__ __forceinline__ UnitDraws unit_draws(const SweepArgs &a, unsigned t, int lane)
 {
     UnitDraws u{0.0, 0.0, false};
@@ -220,7 +255,8 @@ __device__ __forceinline__ UnitDraws unit_draws(const SweepArgs &a, unsigned t, 
 // it, inside a call of lattice sweeps, the caller keeps them).
 __device__ __forceinline__ HyperIn end_of_sweep_draws(const SweepArgs &a, unsigned t, Red r,
                                                       const HyperIn &in, int lane,
-                                                      const UnitDraws &u, bool commit = true)
+                                                      const UnitDraws &u, const TraceTo &trace,
+                                                      bool commit = true)
 {
     double b0 = in.beta0;
     if (a.with_hyper && a.intercept) {
@@ -260,11 +296,10 @@ __device__ __forceinline__ HyperIn end_of_sweep_draws(const SweepArgs &a, unsign
         a.st->rsum = r.rsum;
         if (commit)
             a.st->beta0 = b0;
-        double *const tr = a.st->trace;   // read at run time: batches and graphs see changes
-        if (tr && (long long)t < a.st->trace_cap) {
-            tr[3 * (size_t)t] = v;
-            tr[3 * (size_t)t + 1] = other;
-            tr[3 * (size_t)t + 2] = b0;
+        if (trace.rows && (long long)t < trace.cap) {
+            trace.rows[3 * (size_t)t] = v;
+            trace.rows[3 * (size_t)t + 1] = other;
+            trace.rows[3 * (size_t)t + 2] = b0;
         }
     }
     return HyperIn{v, other, b0};    // valid in lane 0
@@ -274,7 +309,7 @@ __device__ __forceinline__ HyperIn end_of_sweep_draws(const SweepArgs &a, unsign
 __device__ __forceinline__ HyperIn end_of_sweep_draws(const SweepArgs &a, unsigned t, Red r,
                                                       const HyperIn &in, int lane)
 {
-    return end_of_sweep_draws(a, t, r, in, lane, unit_draws(a, t, lane));
+    return end_of_sweep_draws(a, t, r, in, lane, unit_draws(a, t, lane), trace_of(a));
 }
 
 // The persistent kernels draw the unit variates of kUnitBatch sweeps at a
@@ -430,7 +465,8 @@ __device__ __forceinline__ HyperIn fold_draws(const SweepArgs &a, unsigned t, co
             else if (!a.dry)
                 atomicOr(&a.st->status, kStatusUnits);
         }
-        const HyperIn out = end_of_sweep_draws(a, t, r, in, lane, u, commit);
+        const HyperIn out = end_of_sweep_draws(a, t, r, in, lane, u,
+                                               a.dry ? TraceTo{} : trace_of(a), commit);
         if (lane == 0) {
             L.hyp[0] = out.tau;
             L.hyp[1] = out.lam;
@@ -1428,28 +1464,78 @@ __global__ __launch_bounds__(Cfg::NT, (kLatWaves<Real, Cfg>)) void lattice_sweep
                                            fold, plan);
 }
 
-// A lattice that fits one tile, many sweeps in one launch (one block): the
-// field stays in LDS (after a sweep every site of the tile is final, so the
-// next sweep needs no reload), this thread's x, y and accumulators stay in
-// registers, and the end-of-sweep reductions and draws run in the block
-// itself.  Every operation is the one the tile kernel and the end of its
-// sweep perform for a single-tile lattice, in the same order, so the results
-// are bitwise those of tile shape 0.  With a.dry set (timing) it writes only
-// the state buffer that the sweep after the last one would overwrite.
-template <typename Real, typename Cfg, bool B0, bool V2>
-__global__ __launch_bounds__(Cfg::NT) void lattice_persistent_kernel(LatArgs<Real> la, SweepArgs a,
-                                                                     int nsweeps)
+// A lattice that fits one tile, up to kUnitBatch sweeps in one launch (one
+// block): the field stays in LDS (after a sweep every site of the tile is
+// final, so the next sweep needs no reload), this thread's x, y and
+// accumulators stay in registers, and the end-of-sweep reductions and draws
+// run in the block itself.  Every operation is the one the tile kernel and
+// the end of its sweep perform for a single-tile lattice, in the same order,
+// so the results are bitwise those of tile shape 0.  With a.dry set (timing)
+// the chain is left as it is.
+//
+// One block is bound by the length of its chain, and the site normals, which
+// depend only on (site, sweep), were most of it: the ahead kernel draws those
+// of all the launch's sweeps over the whole chip (and the rate-free parts of
+// the end-of-sweep draws), into z in the order this kernel's threads read
+// them: quad i of thread tid in sweep s is the four values from
+// 4 ((s NQ + i) NT + tid).  Per sweep, drawn in place -> ahead: 50 x 50 FP64
+// with intercept 8.2 -> 3.9 us, 64 x 64 4-neighbour FP64 7.3 -> 3.1 us, 64 x 64
+// FP32 5.8 -> 3.4 us.  What is left is the k phases' LDS round trips and the
+// FP64 chain of the end of the sweep.
+template <typename Real, typename Cfg, bool V2>
+__global__ __launch_bounds__(Cfg::NT) void lattice_ahead_kernel(Real *z, SweepArgs a, int rows,
+                                                                int cols, int cnt)
 {
-    constexpr int NT = Cfg::NT, NQ = Cfg::NQ;
+    if ((int)blockIdx.x == cnt * Cfg::NQ) {
+        unit_ring_fill(a, 0, cnt);
+        return;
+    }
+    const int s = (int)blockIdx.x / Cfg::NQ, i = (int)blockIdx.x % Cfg::NQ;
+    const int tid = (int)threadIdx.x;
+    const unsigned t = (unsigned)a.st->sweep + (unsigned)s;
+    const int r = quad_row<Cfg>(tid, i), c = quad_col<Cfg>(tid);
+    if (r >= rows || c >= cols)
+        return;
+    Real v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)     // sites outside the lattice draw too; no one reads them
+        v[k] = lattice_normal<Real, V2>(a, t, r + (k >> 1), c + (k & 1), cols);
+    using L = typename Pair<Real>::Lds;
+    L *const out = reinterpret_cast<L *>(z + 4 * ((size_t)blockIdx.x * Cfg::NT + tid));
+    out[0] = L{v[0], v[1]};
+    out[1] = L{v[2], v[3]};
+}
+
+template <typename Real, typename Cfg>
+__device__ __forceinline__ void load_ahead(Real (&v)[Cfg::NQ][4], const Real *z, int s)
+{
+    using L = typename Pair<Real>::Lds;
+#pragma unroll
+    for (int i = 0; i < Cfg::NQ; ++i) {
+        const L *const p = reinterpret_cast<const L *>(
+            z + 4 * ((size_t)(s * Cfg::NQ + i) * Cfg::NT + threadIdx.x));
+        const L a = p[0], b = p[1];
+        v[i][0] = a.x;
+        v[i][1] = a.y;
+        v[i][2] = b.x;
+        v[i][3] = b.y;
+    }
+}
+
+template <typename Real, typename Cfg, bool B0>
+__global__ __launch_bounds__(Cfg::NT) void lattice_persistent_kernel(LatArgs<Real> la, SweepArgs a,
+                                                                     const Real *z, int nsweeps)
+{
+    constexpr int NT = Cfg::NT, NQ = Cfg::NQ, ST = Cfg::ST;
     __shared__ __align__(16) Real xs[Cfg::LH * Cfg::LW];
-    __shared__ Real qtab[2 * (Cfg::ST + 1)];
+    __shared__ Real qtab[2 * (ST + 1)];
     __shared__ double red[kPartials * (NT / 64)];
     __shared__ double hyp[3];
-    __shared__ UnitDraws ub[kUnitBatch][2];
     const TileAt at{0, 0, la.rows, la.cols};
     const int lane = (int)threadIdx.x & 63;
     unsigned t = (unsigned)a.st->sweep;
     long long nacc = a.st->n_acc;
+    const TraceTo trace = trace_of(a);
     HyperIn in{a.st->tau, a.st->lam, B0 ? a.st->beta0 : 0.0};
     QuadRegs<Real, Cfg> q;
     double s1r[NQ][4], s2r[NQ][4];
@@ -1457,23 +1543,45 @@ __global__ __launch_bounds__(Cfg::NT) void lattice_persistent_kernel(LatArgs<Rea
     load_quads<Real, Cfg, false>(q.y, la.y, at);
     load_quads<double, Cfg, false>(s1r, a.s1, at);
     load_quads<double, Cfg, false>(s2r, a.s2, at);
+    Real znext[NQ][4];
+    load_ahead<Real, Cfg>(znext, z, 0);
     // the ring lies outside the lattice: 0
     for (int i = (int)threadIdx.x; i < Cfg::LH * Cfg::LW; i += NT)
         xs[i] = (Real)0;
     lds_barrier();
     stage_quads<Real, Cfg>(xs, q.x);
+    qtab_fill<Real, ST>(qtab, (Real)in.tau, (Real)in.lam);
+    if (threadIdx.x == 0) {
+        hyp[0] = in.tau;
+        hyp[1] = in.lam;
+        hyp[2] = in.beta0;
+    }
     bool accumulated = false;
     for (int s = 0; s < nsweeps; ++s) {
-        if (s % kUnitBatch == 0) {
-            unit_draw_batch<NT>(a, t, min(kUnitBatch, nsweeps - s), ub);
-            lds_barrier();
-        }
-        const SiteCtx<Real> sc = site_ctx<Real, Cfg::ST, B0>(a, in, qtab);
-        qtab_fill<Real, Cfg::ST>(qtab, sc.tau, sc.lam);
         lds_barrier();
-        Red rd = lattice_phases<Real, Cfg, false, B0, false>(xs, q, at, sc, [&](auto J) {
-            draw_normals<Real, Cfg, decltype(J)::value, false, V2, false>(q, at, a, t);
-        });
+        in = HyperIn{hyp[0], hyp[1], hyp[2]};
+        SiteCtx<Real> sc;
+        sc.tau = (Real)in.tau;
+        sc.lam = (Real)in.lam;
+        sc.tau_rho = (Real)(in.tau * a.rho);
+        sc.beta0 = B0 ? in.beta0 : 0.0;
+        sc.beta0_r = (Real)sc.beta0;
+        sc.inv_q_full = qtab[ST];
+        sc.isd_full = qtab[2 * ST + 1];
+        sc.one_minus_rho = a.one_minus_rho;
+        sc.rho = a.rho;
+        sc.qtab = qtab;
+        // this sweep's normals; the next one's and its unit variates load
+        // while it runs
+#pragma unroll
+        for (int i = 0; i < NQ; ++i)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                q.z[i][k] = znext[i][k];
+        load_ahead<Real, Cfg>(znext, z, min(s + 1, nsweeps - 1));
+        const UnitDraws u = a.with_hyper && threadIdx.x < 2 ? a.units[2 * s + lane]
+                                                            : UnitDraws{0.0, 0.0, false};
+        Red rd = lattice_phases<Real, Cfg, false, B0, false>(xs, q, at, sc, [](auto) {});
         if ((long long)t >= a.burn_in) {
 #pragma unroll
             for (int i = 0; i < NQ; ++i)
@@ -1488,22 +1596,25 @@ __global__ __launch_bounds__(Cfg::NT) void lattice_persistent_kernel(LatArgs<Rea
         }
         block_sum3<NT>(rd.q, rd.sse, rd.rsum, red);
         if (threadIdx.x < 64) {
-            // the end-of-sweep sum over one partial slot: x + 0 + ... = x
-            rd.q = __shfl(rd.q, 0, 64);
-            rd.sse = __shfl(rd.sse, 0, 64);
-            rd.rsum = __shfl(rd.rsum, 0, 64);
-            const HyperIn out = end_of_sweep_draws(a, t, rd, in, lane,
-                                                   ub[s % kUnitBatch][lane < 2 ? lane : 0]);
+            // the end-of-sweep sum over one partial slot: x + 0 + ... = x;
+            // the draws, and the scales the next sweep looks up
+            rd.q = uniform_value(rd.q);
+            rd.sse = uniform_value(rd.sse);
+            rd.rsum = uniform_value(rd.rsum);
+            HyperIn out = end_of_sweep_draws(a, t, rd, in, lane, u, trace);
+            out.tau = uniform_value(out.tau);
+            out.lam = uniform_value(out.lam);
+            qtab_fill<Real, ST>(qtab, (Real)out.tau, (Real)out.lam);
             if (lane == 0) {
                 hyp[0] = out.tau;
                 hyp[1] = out.lam;
                 hyp[2] = out.beta0;
             }
         }
-        lds_barrier();
-        in = HyperIn{hyp[0], hyp[1], hyp[2]};
         ++t;
     }
+    if (a.dry)
+        return;
     // the state after the last sweep: x in buffer t mod 2, the accumulators,
     // the counters (the draws already stored tau, lam, beta0 and reductions)
     Real *dst = (t & 1u) ? la.x1 : la.x0;
@@ -1517,14 +1628,14 @@ __global__ __launch_bounds__(Cfg::NT) void lattice_persistent_kernel(LatArgs<Rea
             if (rr < at.rows && cc < at.cols) {
                 const int g = rr * at.cols + cc;
                 dst[g] = q.x[i][k];
-                if (accumulated && !a.dry) {
+                if (accumulated) {
                     a.s1[g] = s1r[i][k];
                     a.s2[g] = s2r[i][k];
                 }
             }
         }
     }
-    if (threadIdx.x == 0 && !a.dry) {
+    if (threadIdx.x == 0) {
         a.st->n_acc = nacc;
         a.st->sweep = (unsigned long long)t;
     }
@@ -2122,6 +2233,7 @@ __global__ __launch_bounds__(kCsrPersistThreads) void csr_persistent_kernel(CsrA
         xs[p] = ca.x[p];
     CsrScalars v = csr_scalars(a, B0);
     long long nacc = a.st->n_acc;
+    const TraceTo trace = trace_of(a);
     lds_barrier();
     for (int s = 0; s < nsweeps; ++s) {
         if (s % kUnitBatch == 0) {
@@ -2188,7 +2300,8 @@ __global__ __launch_bounds__(kCsrPersistThreads) void csr_persistent_kernel(CsrA
                 r.rsum += red[2 * GW + w];
             }
             const HyperIn out = end_of_sweep_draws(a, v.t, r, HyperIn{v.tau, v.lam, v.beta0},
-                                                   lane, ub[s % kUnitBatch][lane < 2 ? lane : 0]);
+                                                   lane, ub[s % kUnitBatch][lane < 2 ? lane : 0],
+                                                   trace);
             if (lane == 0) {
                 hyp[0] = out.tau;
                 hyp[1] = out.lam;
@@ -2415,6 +2528,7 @@ struct gmrf_chain {
     double *d_partials = nullptr;
     double *d_stats = nullptr;
     UnitDraws *d_units = nullptr;     // ring of unit variates drawn ahead of the sweeps
+    void *d_ahead = nullptr;          // one-tile lattices: normals of kUnitBatch sweeps
     int slot_stride = 0;              // partial slots reserved per buffer (lattice: two)
     int total_slots = 0;              // partial slots of one sweep (current tile shape)
     int lat_tile = 0;                 // shape: lattice tile (index into kTiles); general
@@ -2579,6 +2693,9 @@ size_t chain_layout(const gmrf_graph *g, gmrf_precision p, char *base, gmrf_chai
     char *part = take(8 * kPartials * (size_t)std::max(reserve, 1) * 2);
     char *units = take(sizeof(UnitDraws) * 2 * kUnitRows);
     char *stats = take(16 * n);
+    char *ahead = is_lattice(g) && tile_fits(g->h, kPersistent)
+                      ? take(rs * kTiles[0].th * kTiles[0].tw * kUnitBatch)
+                      : nullptr;
     char *trials = binomial ? take(4 * n) : nullptr;
     char *chunk_off = binomial ? take(4 * (size_t)(n + 1)) : nullptr;
     char *chunk_site = binomial ? take(4 * (size_t)std::max<int64_t>(n_chunks, 1)) : nullptr;
@@ -2601,6 +2718,7 @@ size_t chain_layout(const gmrf_graph *g, gmrf_precision p, char *base, gmrf_chai
         c->d_partials = reinterpret_cast<double *>(part);
         c->d_stats = reinterpret_cast<double *>(stats);
         c->d_units = reinterpret_cast<UnitDraws *>(units);
+        c->d_ahead = ahead;
         c->slot_stride = std::max(reserve, 1);
         c->total_slots = slots;
         c->pass_blocks = pass_blocks;
@@ -2729,23 +2847,34 @@ void launch_lattice(const gmrf_chain *c, const SweepArgs &a, hipStream_t s, hipE
         launch_lattice_shape<Real, ST, 1>(c, a, s, ev0, ev1, rel, fold, plan);
 }
 
-// nsweeps sweeps of a shape-2 chain in one launch of the persistent kernel.
+// nsweeps sweeps of a shape-2 lattice chain: per kUnitBatch sweeps, the draws
+// ahead and the persistent kernel.
 template <typename Real, int ST>
 void launch_persistent_typed(const gmrf_chain *c, const SweepArgs &a, int nsweeps, hipStream_t s,
                              hipEvent_t ev0, hipEvent_t ev1)
 {
     const LatArgs<Real> la = lattice_args<Real>(c);
     using Cfg = LatticeCfg<ST, 0>;
-    const bool v2 = c->model.rng_version == 2;
-    auto kern = c->model.intercept
-                    ? (v2 ? lattice_persistent_kernel<Real, Cfg, true, true>
-                          : lattice_persistent_kernel<Real, Cfg, true, false>)
-                    : (v2 ? lattice_persistent_kernel<Real, Cfg, false, true>
-                          : lattice_persistent_kernel<Real, Cfg, false, false>);
-    if (ev0 || ev1)
-        hipExtLaunchKernelGGL(kern, dim3(1), dim3(Cfg::NT), 0, s, ev0, ev1, 0, la, a, nsweeps);
-    else
-        hipLaunchKernelGGL(kern, dim3(1), dim3(Cfg::NT), 0, s, la, a, nsweeps);
+    Real *const z = static_cast<Real *>(c->d_ahead);
+    auto ahead = c->model.rng_version == 2 ? lattice_ahead_kernel<Real, Cfg, true>
+                                           : lattice_ahead_kernel<Real, Cfg, false>;
+    auto kern = c->model.intercept ? lattice_persistent_kernel<Real, Cfg, true>
+                                   : lattice_persistent_kernel<Real, Cfg, false>;
+    for (int i = 0; i < nsweeps; i += kUnitBatch) {
+        const int cnt = std::min(kUnitBatch, nsweeps - i);
+        const hipEvent_t e0 = i == 0 ? ev0 : nullptr, e1 = i + cnt == nsweeps ? ev1 : nullptr;
+        const dim3 grid(cnt * Cfg::NQ + 1);
+        if (e0)
+            hipExtLaunchKernelGGL(ahead, grid, dim3(Cfg::NT), 0, s, e0, nullptr, 0, z, a, la.rows,
+                                  la.cols, cnt);
+        else
+            hipLaunchKernelGGL(ahead, grid, dim3(Cfg::NT), 0, s, z, a, la.rows, la.cols, cnt);
+        if (e1)
+            hipExtLaunchKernelGGL(kern, dim3(1), dim3(Cfg::NT), 0, s, nullptr, e1, 0, la, a, z,
+                                  cnt);
+        else
+            hipLaunchKernelGGL(kern, dim3(1), dim3(Cfg::NT), 0, s, la, a, z, cnt);
+    }
 }
 
 SlabTable slab_table(const HostGraph &h)
@@ -4355,15 +4484,13 @@ int gmrf_chain_autotune(gmrf_chain *c, int32_t reps, hipStream_t stream, int32_t
         // Whole sweeps (the sweep kernels, or the persistent
         // kernel) in dry mode (dry_args), so the sweep kernels write only the
         // other state buffer, the partial slots and the statistics scratch
-        // and the chain is unchanged; the persistent kernel runs an odd
-        // number of sweeps so that it too ends in the other state buffer.
+        // and the chain is unchanged.
         const SweepArgs a = dry_args(make_args(c, GMRF_WITH_HYPER), c);
-        const int odd = reps | 1;
         if (k == kPersistent) {
             launch_persistent(c, a, 1, stream);
             he = hipEventRecord(e0, stream);
             if (he == hipSuccess)
-                launch_persistent(c, a, odd, stream);
+                launch_persistent(c, a, reps, stream);
         } else {
             launch_sweeps(c, a, 2, stream);
             he = hipEventRecord(e0, stream);
@@ -4379,7 +4506,7 @@ int gmrf_chain_autotune(gmrf_chain *c, int32_t reps, hipStream_t stream, int32_t
         float ms = 0.0f;
         if (he == hipSuccess)
             he = hipEventElapsedTime(&ms, e0, e1);
-        t[k] = 1e3 * (double)ms / (k == kPersistent ? odd : reps);
+        t[k] = 1e3 * (double)ms / reps;
         if (he == hipSuccess && (k == 0 || t[k] < t[win]))
             win = k;
     }
