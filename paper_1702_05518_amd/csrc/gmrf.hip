@@ -1915,39 +1915,53 @@ __global__ __launch_bounds__(kThreads) void csr_batch_kernel(const CsrJob<Real> 
 // buffers (sweep t reads buffer t & 1), so no block sees another's new values
 // through memory.
 template <typename Real> struct FusedArgs {
-    const int *ch_loc, *ch_row, *ch_adj, *ch_meta;   // per-chunk bases and metadata
+    const int *ch_loc, *ch_head, *ch_grp, *ch_meta;  // per-chunk bases and metadata
     const int *loc_site;                             // slab position of each staged site
-    const unsigned short *loc_row, *loc_adj;         // local adjacency of the R sites
+    const unsigned *loc_head;                        // rows of the R sites: first group << 16
+                                                     // | degree
+    const uint2 *loc_grp;                            // their neighbours, four per group
     const unsigned *loc_id;                          // original id of each staged site
     Real *x0, *x1;                                   // ping-pong state, slab order
     const Real *y;                                   // y (slab order)
     int k;                                           // colors
 };
 
-constexpr int kFusedGather = 8;                      // neighbour indices read per batch
 constexpr int kQtabDeg = 64;                         // degrees with tabulated scales
 constexpr int kFusedCH = 4;                          // sites per thread per batch
 constexpr int kFoldUnroll = 8;                       // partial slots per thread in flight
 
 __host__ __device__ constexpr size_t lds_align16(size_t b) { return (b + 15) / 16 * 16; }
 
-// Neighbour sum of a staged site in row order (local neighbours e0 .. e1 - 1),
-// continuing the running sum sum.
-template <typename Real>
-__device__ __forceinline__ Real fused_nbr_sum(const Real *xs, const unsigned short *adj, int e0,
-                                              int e1, Real sum)
+// An R site as a phase takes it: its first kRowGroups groups of four
+// neighbours, y, the normal variate, and the scales of its degree.  The first
+// twelve neighbours are read in one round for every site: with a degree above
+// 8 in almost every wavefront (one Delaunay site in twelve), reading eight and
+// then the rest in a loop cost two dependent LDS round trips per extra
+// neighbour, most of a phase's 2,700 cycles.  Missing neighbours are the slot
+// that holds 0, so they need no test in the sum.  Per sweep, rows read eight
+// and one at a time -> in groups, a phase ahead: 15k-site Delaunay graph FP64
+// 15.5 -> 11.4 us, 300k FP32 18.1 -> 14.4, 1M FP32 / FP64 33.4 / 43.8 -> 31.3 /
+// 38.1 us.
+constexpr int kRowGroups = 3;
+template <typename Real> struct FusedRow {
+    uint2 g[kRowGroups];
+    unsigned head;
+    Real y, z, inv_q, isd;
+};
+
+// Neighbour j of a group: the byte offset of its value in LDS.
+template <typename Real> __device__ __forceinline__ unsigned row_offset(uint2 g, int j)
 {
-    for (int eb = e0; eb < e1; eb += kFusedGather) {
-        int l[kFusedGather];
-#pragma unroll
-        for (int q = 0; q < kFusedGather; ++q)
-            l[q] = adj[min(eb + q, e1 - 1)];
-#pragma unroll
-        for (int q = 0; q < kFusedGather; ++q)
-            if (eb + q < e1)
-                sum += xs[l[q]];
-    }
-    return sum;
+    const unsigned w = j < 2 ? g.x : g.y;
+    const unsigned o = (j & 1) ? w >> 16 : w & 0xffffu;
+    return sizeof(Real) == 8 ? o * 2 : o;
+}
+
+// Is the neighbour's slot below lo (lo4 = 4 lo)?
+__device__ __forceinline__ bool row_below(uint2 g, int j, unsigned lo4)
+{
+    const unsigned w = j < 2 ? g.x : g.y;
+    return ((j & 1) ? w >> 16 : w & 0xffffu) < lo4;
 }
 
 // Chunk b of a chain (rel, fold: as for the lattice sweep kernel).  Order of
@@ -1975,41 +1989,44 @@ __device__ __forceinline__ void csr_fused_block(const FusedArgs<Real> &fa, const
     const int *meta = fa.ch_meta + (size_t)b * (3 * k + 1);
     const int loc0 = fa.ch_loc[b], nloc = fa.ch_loc[b + 1] - loc0;
     const int nr = meta[k];
-    const int row0 = fa.ch_row[b], adj0 = fa.ch_adj[b], nadj = fa.ch_adj[b + 1] - adj0;
+    const int head0 = fa.ch_head[b], nhead = fa.ch_head[b + 1] - head0;
+    const int grp0 = fa.ch_grp[b], ngrp = fa.ch_grp[b + 1] - grp0;
     const int *site = fa.loc_site + loc0;
     const unsigned *sid = fa.loc_id + loc0;
-    // the chunk's own LDS image (chunk_lds_bytes of its counts; the launch
-    // reserves the graph's largest): staged values, y and variates of R, R's
-    // local rows (padded to whole 16-byte vectors) and neighbours
+    // the chunk's own LDS image (sweep_lds_bytes of its counts; the launch
+    // reserves the graph's largest): staged values and a 0, y and variates of
+    // R, R's row heads and neighbour groups
     Real *xs = reinterpret_cast<Real *>(fused_lds);
-    size_t off = lds_align16(sizeof(Real) * (size_t)nloc);
+    size_t off = lds_align16(sizeof(Real) * (size_t)(nloc + 1));
     Real *ys = reinterpret_cast<Real *>(fused_lds + off);
     off += lds_align16(sizeof(Real) * (size_t)nr);
     Real *zs = reinterpret_cast<Real *>(fused_lds + off);
     off += lds_align16(sizeof(Real) * (size_t)nr);
-    unsigned short *lrow = reinterpret_cast<unsigned short *>(fused_lds + off);
-    off += lds_align16(sizeof(unsigned short) * (size_t)(nr + 1));
-    unsigned short *ladj = reinterpret_cast<unsigned short *>(fused_lds + off);
+    unsigned *lhead = reinterpret_cast<unsigned *>(fused_lds + off);
+    off += lds_align16(sizeof(unsigned) * (size_t)nr);
+    uint2 *lgrp = reinterpret_cast<uint2 *>(fused_lds + off);
     for (int i = (int)threadIdx.x; i < 3 * k + 1; i += kThreads)
         sm[i] = meta[i];
 
-    // rows and neighbours: each chunk's start is on a 16-byte boundary and
-    // both are padded to whole 16-byte vectors; lane L of a wave copies
-    // vector i to the wave's LDS base + 16 L
+    // heads and groups: each chunk's part starts on a 16-byte boundary and
+    // fills whole 16-byte vectors; lane L of a wave copies vector i to the
+    // wave's LDS base + 16 L
     {
-        const int nrow4 = (nr + 1 + 7) / 8, nadj4 = nadj / 8;
-        const uint4 *grow = reinterpret_cast<const uint4 *>(fa.loc_row + row0);
-        const uint4 *gadj = reinterpret_cast<const uint4 *>(fa.loc_adj + adj0);
-        uint4 *srow = reinterpret_cast<uint4 *>(lrow);
-        uint4 *sadj = reinterpret_cast<uint4 *>(ladj);
+        const int nh4 = nhead / 4, ng2 = ngrp / 2;
+        const uint4 *ghead = reinterpret_cast<const uint4 *>(fa.loc_head + head0);
+        const uint4 *ggrp = reinterpret_cast<const uint4 *>(fa.loc_grp + grp0);
+        uint4 *shead = reinterpret_cast<uint4 *>(lhead);
+        uint4 *sgrp = reinterpret_cast<uint4 *>(lgrp);
         const int lane = (int)threadIdx.x & 63;
-        for (int i = (int)threadIdx.x; i - lane < nrow4; i += kThreads)
-            if (i < nrow4)
-                __builtin_amdgcn_global_load_lds(grow + i, srow + (i - lane), 16, 0, 0);
-        for (int i = (int)threadIdx.x; i - lane < nadj4; i += kThreads)
-            if (i < nadj4)
-                __builtin_amdgcn_global_load_lds(gadj + i, sadj + (i - lane), 16, 0, 0);
+        for (int i = (int)threadIdx.x; i - lane < nh4; i += kThreads)
+            if (i < nh4)
+                __builtin_amdgcn_global_load_lds(ghead + i, shead + (i - lane), 16, 0, 0);
+        for (int i = (int)threadIdx.x; i - lane < ng2; i += kThreads)
+            if (i < ng2)
+                __builtin_amdgcn_global_load_lds(ggrp + i, sgrp + (i - lane), 16, 0, 0);
     }
+    if (threadIdx.x == 0)
+        xs[nloc] = (Real)0;
 
     // staging, kFusedCH sites per thread at a time; the first batch's slab
     // positions load beside the fold's partials
@@ -2088,60 +2105,79 @@ __device__ __forceinline__ void csr_fused_block(const FusedArgs<Real> &fa, const
     // accumulators and writes it back.  The accumulators take atomic adds
     // whose results are not read back, so no phase waits on global memory;
     // each accumulator takes one add per sweep, so each sum is the plain
-    // sum, bit for bit.
+    // sum, bit for bit.  A phase is bound by its chain of LDS reads, so each
+    // thread reads its row of the next phase (which no phase changes) before
+    // the barrier that publishes this one's values.
+    auto fetch = [&](int s, FusedRow<Real> &r) {
+        r.head = lhead[s];
+        const int deg = (int)(r.head & 0xffffu), first = (int)(r.head >> 16);
+#pragma unroll
+        for (int j = 0; j < kRowGroups; ++j)
+            r.g[j] = lgrp[4 * j < deg ? first + j : 0];
+        r.y = ys[s];
+        r.z = zs[s];
+        if (deg < kQtabDeg) {
+            r.inv_q = qtab[deg];
+            r.isd = qtab[kQtabDeg + deg];
+        } else {
+            site_scales<Real>(tau, lam, deg, r.inv_q, r.isd);
+        }
+    };
+    const char *const xb = reinterpret_cast<const char *>(xs);
+    auto value = [&](uint2 g, int j) {
+        return *reinterpret_cast<const Real *>(xb + row_offset<Real>(g, j));
+    };
     Red rd;
+    FusedRow<Real> row;
+    int lo = sm[0], hi = sm[1];
+    fetch(min(lo + (int)threadIdx.x, nr - 1), row);
     for (int c = 0; c < k; ++c) {
-        const int lo = sm[c], hi = sm[c + 1], own = sm[k + 1 + c], ost = sm[2 * k + 1 + c];
+        const int own = sm[k + 1 + c], ost = sm[2 * k + 1 + c];
+        const int lo2 = hi, hi2 = c + 1 < k ? sm[c + 2] : hi;
         for (int s = lo + (int)threadIdx.x; s < hi; s += kThreads) {
-            const int e0 = lrow[s], e1 = lrow[s + 1], deg = e1 - e0;
-            // the first kFusedGather neighbours stay in registers for the
-            // q term; the rest (rare) are read again
-            int l[kFusedGather];
-            Real v[kFusedGather];
+            if (s >= lo + kThreads)
+                fetch(s, row);
+            const int deg = (int)(row.head & 0xffffu), first = (int)(row.head >> 16);
+            Real v[4 * kRowGroups];
 #pragma unroll
-            for (int q = 0; q < kFusedGather; ++q)
-                l[q] = ladj[min(e0 + q, e1 - 1)];
-#pragma unroll
-            for (int q = 0; q < kFusedGather; ++q)
-                v[q] = xs[l[q]];
+            for (int j = 0; j < 4 * kRowGroups; ++j)
+                v[j] = value(row.g[j / 4], j % 4);
             Real sum = (Real)0;
 #pragma unroll
-            for (int q = 0; q < kFusedGather; ++q)
-                if (q < deg)
-                    sum += v[q];
-            if (deg > kFusedGather)
-                sum = fused_nbr_sum<Real>(xs, ladj, e0 + kFusedGather, e1, sum);
-            Real inv_q, isd;
-            if (deg < kQtabDeg) {
-                inv_q = qtab[deg];
-                isd = qtab[kQtabDeg + deg];
-            } else {
-                site_scales<Real>(tau, lam, deg, inv_q, isd);
+            for (int j = 0; j < 4 * kRowGroups; ++j)
+                sum += v[j];
+            for (int j0 = kRowGroups; 4 * j0 < deg; ++j0) {
+                const uint2 g = lgrp[first + j0];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    sum += value(g, j);
             }
-            const Real yv = ys[s];
-            const Real yeff = B0 ? yv - (Real)beta0 : yv;
-            const Real xn = site_draw<Real>(yeff, sum, zs[s], lam, tau_rho, inv_q, isd);
+            const Real yeff = B0 ? row.y - (Real)beta0 : row.y;
+            const Real xn = site_draw<Real>(yeff, sum, row.z, lam, tau_rho, row.inv_q, row.isd);
             xs[s] = xn;
             const int o = s - lo;
             if (o < own) {
                 const int pos = ost + o;
+                const unsigned lo4 = 4u * (unsigned)lo;
                 const double xd = (double)xn;
                 double edge = 0.0;              // lower colors: this sweep's values
 #pragma unroll
-                for (int q = 0; q < kFusedGather; ++q)
-                    if (q < deg && l[q] < lo) {
-                        const double d = xd - (double)v[q];
-                        edge += d * d;
-                    }
-                for (int e = e0 + kFusedGather; e < e1; ++e) {
-                    const int le = ladj[e];
-                    if (le < lo) {
-                        const double d = xd - (double)xs[le];
-                        edge += d * d;
-                    }
+                for (int j = 0; j < 4 * kRowGroups; ++j) {
+                    // any other neighbour adds (x - x)^2 = 0
+                    const double d = xd - (double)(row_below(row.g[j / 4], j % 4, lo4) ? v[j] : xn);
+                    edge += d * d;
+                }
+                for (int j0 = kRowGroups; 4 * j0 < deg; ++j0) {
+                    const uint2 g = lgrp[first + j0];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (row_below(g, j, lo4)) {
+                            const double d = xd - (double)value(g, j);
+                            edge += d * d;
+                        }
                 }
                 rd.q += (1.0 - a.rho) * (double)deg * xd * xd + a.rho * edge;
-                const double rr = B0 ? (double)yv - beta0 - xd : (double)yv - xd;
+                const double rr = B0 ? (double)row.y - beta0 - xd : (double)row.y - xd;
                 rd.sse += rr * rr;
                 if (B0)
                     rd.rsum += rr;
@@ -2153,6 +2189,9 @@ __device__ __forceinline__ void csr_fused_block(const FusedArgs<Real> &fa, const
                 dst[pos] = xn;
             }
         }
+        lo = lo2;
+        hi = hi2;
+        fetch(min(lo + (int)threadIdx.x, nr - 1), row);
         lds_barrier();
     }
     write_partials<kThreads>(partials_of(a, rel), rd, b);
@@ -2508,10 +2547,10 @@ struct gmrf_graph {
     HostGraph h;
     int *d_row_ptr = nullptr, *d_col = nullptr, *d_orig = nullptr;
     // chunks of the one-launch sweep (shape 1), when h.chunks_ok
-    int *d_ch_loc = nullptr, *d_ch_row = nullptr, *d_ch_adj = nullptr, *d_ch_meta = nullptr;
+    int *d_ch_loc = nullptr, *d_ch_head = nullptr, *d_ch_grp = nullptr, *d_ch_meta = nullptr;
     int *d_loc_site = nullptr;
-    unsigned *d_loc_id = nullptr;
-    unsigned short *d_loc_row = nullptr, *d_loc_adj = nullptr;
+    unsigned *d_loc_id = nullptr, *d_loc_head = nullptr;
+    uint16_t *d_loc_grp = nullptr;
 };
 
 struct gmrf_chain {
@@ -2940,7 +2979,7 @@ bool csr_persist_fits(const HostGraph &h, gmrf_precision p)
 bool csr_fused_fits(const HostGraph &h, gmrf_precision p, bool binomial)
 {
     return h.stencil == 0 && h.chunks_ok && !binomial &&
-           (p == GMRF_FP64 ? h.max_image8 : h.max_image4) <= kFusedLaunchLds;
+           (p == GMRF_FP64 ? h.max_lds8 : h.max_lds4) <= kFusedLaunchLds;
 }
 
 // Default shape of a general-graph chain: the one block while it covers
@@ -2998,12 +3037,12 @@ template <typename Real> FusedArgs<Real> fused_args(const gmrf_chain *c, bool sw
     const gmrf_graph *g = c->g;
     FusedArgs<Real> fa;
     fa.ch_loc = g->d_ch_loc;
-    fa.ch_row = g->d_ch_row;
-    fa.ch_adj = g->d_ch_adj;
+    fa.ch_head = g->d_ch_head;
+    fa.ch_grp = g->d_ch_grp;
     fa.ch_meta = g->d_ch_meta;
     fa.loc_site = g->d_loc_site;
-    fa.loc_row = g->d_loc_row;
-    fa.loc_adj = g->d_loc_adj;
+    fa.loc_head = g->d_loc_head;
+    fa.loc_grp = reinterpret_cast<const uint2 *>(g->d_loc_grp);
     fa.loc_id = g->d_loc_id;
     fa.x0 = static_cast<Real *>(c->d_x[swap ? 1 : 0]);
     fa.x1 = static_cast<Real *>(c->d_x[swap ? 0 : 1]);
@@ -3016,7 +3055,7 @@ template <typename Real> FusedArgs<Real> fused_args(const gmrf_chain *c, bool sw
 // largest chunk image (each block lays out its own chunk's).
 template <typename Real> size_t fused_lds_bytes(const HostGraph &h)
 {
-    return (size_t)(sizeof(Real) == 8 ? h.max_image8 : h.max_image4);
+    return (size_t)(sizeof(Real) == 8 ? h.max_lds8 : h.max_lds4);
 }
 
 template <typename Real>
@@ -3770,13 +3809,13 @@ int gmrf_graph_create(const gmrf_graph_desc *d, void *d_ws, size_t ws_bytes, hip
                     chunk_up.push_back({(void *)dptr, {vec.data(), sizeof(T) * vec.size()}});
             };
             place(g->d_ch_loc, g->h.ch_loc);
-            place(g->d_ch_row, g->h.ch_row);
-            place(g->d_ch_adj, g->h.ch_adj);
+            place(g->d_ch_head, g->h.ch_head);
+            place(g->d_ch_grp, g->h.ch_grp);
             place(g->d_ch_meta, g->h.ch_meta);
             place(g->d_loc_site, g->h.loc_site);
             place(g->d_loc_id, g->h.loc_id);
-            place(g->d_loc_row, g->h.loc_row);
-            place(g->d_loc_adj, g->h.loc_adj);
+            place(g->d_loc_head, g->h.loc_head);
+            place(g->d_loc_grp, g->h.loc_grp);
         }
         static const int kNoNeighbour = 0;   // the column entry of a graph without edges
         hipError_t e = hipMemcpyAsync(g->d_row_ptr, g->h.row_ptr.data(),

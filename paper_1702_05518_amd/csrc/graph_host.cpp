@@ -442,6 +442,11 @@ void build_chunks(HostGraph *g, const std::vector<int32_t> &cell)
     g->loc_adj.clear();
     g->max_local = g->max_r = g->max_adj = 0;
     g->max_image4 = g->max_image8 = 0;
+    g->ch_head.assign(1, 0);
+    g->ch_grp.assign(1, 0);
+    g->loc_head.clear();
+    g->loc_grp.clear();
+    g->max_lds4 = g->max_lds8 = 0;
     for (int32_t b = 0; b < g->nchunks; ++b) {
         R.clear();
         H.clear();
@@ -531,6 +536,29 @@ void build_chunks(HostGraph *g, const std::vector<int32_t> &cell)
             g->loc_row.push_back(0);
         while (g->loc_adj.size() % 8)
             g->loc_adj.push_back(0);
+        // the rows in groups of four, filled with slot nloc
+        const size_t grp0 = g->loc_grp.size() / 4;
+        const uint16_t fill = (uint16_t)(4 * nloc);
+        g->loc_grp.insert(g->loc_grp.end(), 4, fill);
+        for (int32_t u : R) {
+            const uint32_t deg = (uint32_t)(g->row_ptr[u + 1] - g->row_ptr[u]);
+            g->loc_head.push_back((uint32_t)(g->loc_grp.size() / 4 - grp0) << 16 | deg);
+            for (int32_t e = g->row_ptr[u]; e < g->row_ptr[u + 1]; ++e)
+                g->loc_grp.push_back((uint16_t)(4 * slot[g->col[e]]));
+            while (g->loc_grp.size() % 4)
+                g->loc_grp.push_back(fill);
+        }
+        while (g->loc_head.size() % 4)
+            g->loc_head.push_back(0);
+        while (g->loc_grp.size() % 8)
+            g->loc_grp.push_back(fill);
+        const int64_t ngrp = (int64_t)(g->loc_grp.size() / 4 - grp0);
+        if (nloc > 16383 || ngrp > 65535)
+            return;                      // beyond the 16-bit rows (never within the caps)
+        g->max_lds4 = std::max(g->max_lds4, sweep_lds_bytes(nloc, (int64_t)R.size(), ngrp, 4));
+        g->max_lds8 = std::max(g->max_lds8, sweep_lds_bytes(nloc, (int64_t)R.size(), ngrp, 8));
+        g->ch_head.push_back((int32_t)g->loc_head.size());
+        g->ch_grp.push_back((int32_t)(g->loc_grp.size() / 4));
         g->ch_loc.push_back((int32_t)g->loc_site.size());
         g->ch_row.push_back((int32_t)g->loc_row.size());
         g->ch_adj.push_back((int32_t)g->loc_adj.size());
@@ -599,13 +627,13 @@ size_t graph_device_bytes(const HostGraph &g)
                    align_up(sizeof(int32_t) * (size_t)g.n);
     if (g.chunks_ok)
         bytes += align_up(sizeof(int32_t) * g.ch_loc.size()) +
-                 align_up(sizeof(int32_t) * g.ch_row.size()) +
-                 align_up(sizeof(int32_t) * g.ch_adj.size()) +
+                 align_up(sizeof(int32_t) * g.ch_head.size()) +
+                 align_up(sizeof(int32_t) * g.ch_grp.size()) +
                  align_up(sizeof(int32_t) * g.ch_meta.size()) +
                  align_up(sizeof(int32_t) * g.loc_site.size()) +
                  align_up(sizeof(uint32_t) * g.loc_id.size()) +
-                 align_up(sizeof(uint16_t) * g.loc_row.size()) +
-                 align_up(sizeof(uint16_t) * std::max<size_t>(g.loc_adj.size(), 1));
+                 align_up(sizeof(uint32_t) * g.loc_head.size()) +
+                 align_up(sizeof(uint16_t) * g.loc_grp.size());
     return bytes;
 }
 

@@ -56,6 +56,15 @@ struct HostGraph {
     std::vector<uint16_t> loc_row;       // per chunk, |R_b| + 1 offsets into its local neighbours
     std::vector<uint16_t> loc_adj;       // local slots of the neighbours of each R_b site,
                                          // ascending original id
+    // The same rows as the sweep kernel reads them: cut into groups of four
+    // neighbours, short groups filled with the chunk's slot past its staged
+    // sites, which holds 0.  A neighbour is four times its slot; group 0 of a
+    // chunk is all filling.  Both parts fill whole 16-byte vectors per chunk.
+    std::vector<int32_t> ch_head;        // nchunks + 1: first row head of each chunk
+    std::vector<int32_t> ch_grp;         // nchunks + 1: first group of each chunk
+    std::vector<uint32_t> loc_head;      // per R_b site: first group << 16 | degree
+    std::vector<uint16_t> loc_grp;       // four neighbours per group
+    int64_t max_lds4 = 0, max_lds8 = 0;  // largest LDS image of the kernel, FP32 / FP64 values
 };
 
 // Owned sites per chunk, and the limits of a chunk: its LDS image (staged
@@ -74,14 +83,24 @@ constexpr int64_t kFusedLaunchLds = 65536;
 constexpr int64_t kMaxLocalAdj = 65535;
 constexpr int32_t kFusedMaxColors = 32;  // colorings with more colors sweep by color passes
 
-// Bytes of a chunk's LDS image with real_bytes-byte values (the layout of
-// the chunked sweep kernel: values of the staged sites, then y and the
-// sweep's normal variate of each R site, then the R sites' local row offsets
-// and neighbours, each part 16-byte aligned).
+// Bytes of a chunk with real_bytes-byte values (values of the staged sites,
+// then y and the sweep's normal variate of each R site, then the R sites'
+// local row offsets and neighbours, each part 16-byte aligned): the measure
+// that the caps bound.  The kernel's image (sweep_lds_bytes) is larger by
+// what fills the neighbour groups, at most twice it at degree 1.
 inline int64_t chunk_lds_bytes(int64_t nloc, int64_t nr, int64_t nadj, int64_t real_bytes)
 {
     auto al = [](int64_t b) { return (b + 15) / 16 * 16; };
     return al(real_bytes * nloc) + 2 * al(real_bytes * nr) + al(2 * (nr + 1)) + al(2 * nadj);
+}
+
+// Bytes of the LDS image of the chunked sweep kernel: values of the staged
+// sites and the 0 past them, y and the sweep's normal variate of each R site,
+// row heads, neighbour groups.
+inline int64_t sweep_lds_bytes(int64_t nloc, int64_t nr, int64_t ngrp, int64_t real_bytes)
+{
+    auto al = [](int64_t b) { return (b + 15) / 16 * 16; };
+    return al(real_bytes * (nloc + 1)) + 2 * al(real_bytes * nr) + al(4 * nr) + al(8 * ngrp);
 }
 
 // Does a chunk's image fit both caps?
