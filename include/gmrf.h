@@ -36,7 +36,7 @@
  * of m_i PG(1, .) terms, Devroye's alternating-series sampler).  Since psi_i
  * depends only on beta0 and site i's own value, which no earlier color pass
  * changes, the library draws every psi_i of a sweep before the color passes
- * (one launch for all terms, in chunks of 2, then one sum per site); then
+ * (one launch for all terms, in chunks of one site's, then one sum per site); then
  *     Qii = tau * D_ii + psi_i,
  *     m_i = (kappa_i - psi_i beta0 + tau * rho * sum_{j~i} x_j) / Qii,
  * and after the sweep beta0 ~ N(sum(kappa - psi x) / P, 1/P),

@@ -2437,18 +2437,61 @@ __global__ __launch_bounds__(kCsrPersistThreads) void csr_persistent_kernel(CsrA
 // are drawn before the color passes:
 //   * the envelope kernel, one thread per site;
 //   * the term kernel: the terms of all sites are cut into chunks of
-//     kPgChunk consecutive terms of one site, one thread per chunk over the
-//     whole graph (so work is spread evenly whatever the m_p).  Chunk q runs
+//     kPgFew or kPgMany consecutive terms of one site, one lane per chunk over
+//     the whole graph (so work is spread evenly whatever the m_p).  Chunk q runs
 //     on lane q mod 64 and the chunks of a site are consecutive, so a site's
 //     chunks fall into one run of lanes per wavefront; a segmented scan over
 //     the lanes leaves each run's sum in its last chunk's slot;
 //   * the psi kernel, one wavefront per site: psi_p is the sum of the site's
-//     run sums (at most m_p / (64 kPgChunk) + 2 of them), lane l taking runs
+//     run sums (at most m_p / (64 kPgFew) + 2 of them), lane l taking runs
 //     l, l + 64, ... and a fixed tree joining the lanes.
 // Each color pass then runs one thread per site: x_p ~ N(m, 1/Q) with
 // Q = tau D_pp + psi_p, m = (kappa_p - psi_p beta0 + tau rho sum_{j~p} x_j) / Q.
 constexpr int kPsiSites = kThreads / 64;        // sites per block of the psi kernel
-constexpr int kPgChunk = 4;                     // PG(1, .) terms per chunk
+
+// PG(1, .) terms per chunk.  Long chunks keep the lists of a wavefront full,
+// short ones make more wavefronts.  A sweep in FP64, with chunks of 2 / 8, of
+// 0.9 million terms (8,000 sites): 66.4 / 67.9 us; of 0.06 million (500 sites)
+// 34.0 / 39.8; of 1.6 million (14,926 sites) 84.0 / 77.9; of 5.1 million 138
+// / 114.  The line is at two wavefronts of 512 terms per SIMD.
+constexpr int kPgFew = 2, kPgMany = 8;
+constexpr int64_t kPgManyTerms = 1 << 20;
+
+// What a wavefront of the term kernel keeps in LDS: per term, the words or
+// the number its next step needs and in the end its value; two lists of terms
+// (each used from both ends); and the data of the chunk of each lane.
+template <int Chunk>
+struct PgWave {
+    uint64_t slot[64 * Chunk];
+    uint16_t list[64 * Chunk], done[64 * Chunk];
+    PgEnvelope env[64];
+    uint32_t site[64], j0[64];
+};
+constexpr int kPgTryBits = 7, kPgTries = (1 << kPgTryBits) - 2;
+static_assert(64 * kPgMany <= 1 << (16 - kPgTryBits), "a list entry holds a term and its tries");
+
+// The tables that the term kernel reads and the run sums that it writes.
+struct PgArgs {
+    const int *chunk_site, *chunk_off, *trials, *orig;
+    const PgEnvelope *env;
+    double *chunk_sum;
+};
+
+// Orders a wavefront's LDS accesses for the compiler (the hardware executes
+// them in order).
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
+// Lanes below this one whose bit is set.
+__device__ __forceinline__ int lane_rank(unsigned long long mask)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                          __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+}
 
 // The PG envelope of sites lo .. lo + cnt - 1 (tilt beta0 + x_p), so that
 // the term kernel's threads need not each evaluate its erfc and exp.  Run
@@ -2468,30 +2511,165 @@ __global__ __launch_bounds__(kThreads) void pg_env_kernel(CsrArgs<Real> ca, Swee
 
 // Chunks 0 .. nq - 1; the grid is whole blocks of whole wavefronts, so chunk
 // q runs on lane q mod 64.
-template <typename Real, bool B0>
-__global__ __launch_bounds__(kThreads) void pg_chunk_kernel(CsrArgs<Real> ca, SweepArgs a, int nq)
+//
+// Bound by the issue of vector instructions, and by how many lanes they
+// serve: a term takes the right piece (58% of them at small tilts) or the
+// left, the left piece searches 1.4 pairs on average, and one loop over a
+// lane's terms makes every wavefront walk both pieces and wait for its
+// unluckiest lane's search (857 instructions per 64 terms, 129 us per 5
+// million).  So the terms of a wavefront go through the steps of the draw in
+// lists: the choice of the piece for all; the right piece's terms; one draw
+// of the left piece's steep method; tries of its search, the terms without a
+// pair listed again; the values of the search; and for the few terms left (a
+// value not kept or not inside, a series test that is not clear) the draw as
+// written.  Every term takes the same uniforms as when drawn alone: its stream
+// is keyed by (site, term).  A sweep of 14,926 sites and 5.1 million terms
+// took 154 us with one loop per lane and takes 114 (of which this kernel 113
+// and 70); with tilts around -6, 164 and 123.
+template <int Chunk>
+__global__ __launch_bounds__(kThreads) void pg_chunk_kernel(PgArgs ca, SweepArgs a, int nq)
 {
+    constexpr int kPgItems = 64 * Chunk;    // terms of a wavefront
+    __shared__ PgWave<Chunk> waves[kThreads / 64];
+    PgWave<Chunk> &W = waves[threadIdx.x >> 6];
     const int q = (int)blockIdx.x * kThreads + (int)threadIdx.x;
     const int lane = (int)threadIdx.x & 63;
     const bool valid = q < nq;
     const int p = valid ? ca.chunk_site[q] : -1;
-    double sum = 0.0;
+    const unsigned t = (unsigned)a.st->sweep;
+    int cnt = 0;                            // terms of this lane's chunk
+    uint32_t j0 = 0, id = 0;
+    PgEnvelope env{0.0, 1.0, 0.0};
     if (valid) {
-        const int m = ca.trials[p];
-        const int j0 = (q - ca.chunk_off[p]) * kPgChunk;
-        const int j1 = min(j0 + kPgChunk, m);
-        const unsigned t = (unsigned)a.st->sweep;
-        const unsigned id = (unsigned)ca.orig[p];
-        const PgEnvelope env = ca.env[p];      // drawn with beta0 by pg_env_kernel<Real, B0>
-        bool ok = true;
-        for (int j = j0; j < j1; ++j) {
-            double v = 0.0;
-            ok = pg1_draw(env, a.seed, id, t, a.instance, (unsigned)j, &v) && ok;
-            sum += v;
-        }
-        if (!ok)
-            atomicOr(&a.st->status, kStatusGamma);
+        j0 = (uint32_t)((q - ca.chunk_off[p]) * Chunk);
+        cnt = min(Chunk, ca.trials[p] - (int)j0);
+        id = (uint32_t)ca.orig[p];
+        env = ca.env[p];                    // drawn with beta0 by pg_env_kernel<Real, B0>
     }
+    W.env[lane] = env;
+    W.site[lane] = id;
+    W.j0[lane] = j0;
+    auto block = [&](int item, uint32_t m) {      // block m of a term's stream
+        const int l = item & 63;
+        return draw_words(a.seed, W.site[l], t, a.instance,
+                          0x80000000u | ((W.j0[l] + (uint32_t)(item >> 6)) << 10) | m);
+    };
+    auto first_half = [](const Words4 &w) { return open_uniform_f64(w.w0, w.w1); };
+    auto second_half = [](const Words4 &w) { return (uint64_t)w.w2 << 32 | w.w3; };
+    auto unit_of = [](uint64_t w) { return open_uniform_f64((uint32_t)(w >> 32), (uint32_t)w); };
+    int nl = 0, nr = 0;     // in list: left (search), right (from the end)
+    int nf = 0, ng = 0;     // in done: left (steep, then found), general (from the end)
+    auto push = [&](uint16_t *where, int dir, int &n, bool on, int entry) {
+        const unsigned long long m = __ballot(on);
+        if (on)
+            where[dir * (n + lane_rank(m))] = (uint16_t)entry;
+        n += __popcll(m);
+    };
+    uint16_t *const list_end = W.list + kPgItems - 1, *const done_end = W.done + kPgItems - 1;
+
+    // The piece of each term; its stream's block 0 serves the choice and the
+    // next uniform.
+#pragma unroll 1
+    for (int i = 0; i < Chunk; ++i) {
+        const bool on = i < cnt;
+        if (!__any(on))
+            break;
+        const int item = i * 64 + lane;
+        const Words4 w = draw_words(a.seed, id, t, a.instance,
+                                    0x80000000u | ((j0 + (uint32_t)i) << 10));
+        const bool right = first_half(w) < env.right, search = env.z < 1.0 / kPgT;
+        W.slot[item] = second_half(w);
+        push(list_end, -1, nr, on && right, item);
+        push(W.list, 1, nl, on && !right && search, item);
+        push(W.done, 1, nf, on && !right && !search, item);
+    }
+    wave_lds_sync();
+
+    // The right piece.
+#pragma unroll 1
+    for (int b = 0; b < nr; b += 64) {
+        const bool on = b + lane < nr;
+        const int item = list_end[-min(b + lane, nr - 1)];
+        const double x = pg_right_value(W.env[item & 63].K, unit_of(W.slot[item]));
+        const bool ok = pg_series_clear(x, first_half(block(item, 1u)));
+        if (on)
+            W.slot[item] = ok ? __builtin_bit_cast(uint64_t, 0.25 * x) : 0u;
+        push(done_end, -1, ng, on && !ok, item);
+    }
+    // The left piece at steep tilts: one draw (from the end of the list: the
+    // general list grows into the entries already taken).
+#pragma unroll 1
+    for (int b = nf; b > 0; b -= 64) {
+        const bool on = b - 1 - lane >= 0;
+        const int item = W.done[max(b - 1 - lane, 0)];
+        const Words4 w = block(item, 1u);
+        const double x = pg_steep_value(1.0 / W.env[item & 63].z, unit_of(W.slot[item]),
+                                        first_half(w), unit_of(second_half(w)));
+        const bool in = x < kPgT, ok = in && pg_series_clear(x, first_half(block(item, 2u)));
+        wave_lds_sync();
+        if (on)     // not inside: the next draw starts with uniform 4
+            W.slot[item] = ok ? __builtin_bit_cast(uint64_t, 0.25 * x) : in ? 0u : 4u;
+        push(done_end, -1, ng, on && !ok, item);
+        wave_lds_sync();
+    }
+    nf = 0;
+    // The left piece's search: try k pairs the second half of block k (the
+    // term's slot) with the first half of block k + 1.
+    while (nl > 0) {
+        int again = 0;
+#pragma unroll 1
+        for (int b = 0; b < nl; b += 64) {
+            const bool on = b + lane < nl;
+            const int entry = W.list[min(b + lane, nl - 1)];
+            const int item = entry & (kPgItems - 1), k = entry / kPgItems;
+            const Words4 w = block(item, (uint32_t)k + 1u);
+            const bool ok = pg_pair_ok(unit_of(W.slot[item]), first_half(w));
+            const bool retry = !ok && k < kPgTries;
+            wave_lds_sync();                // every entry of this round is read
+            if (on && !ok)
+                W.slot[item] = retry ? second_half(w) : 0u;
+            push(W.list, 1, again, on && retry, entry + kPgItems);
+            push(W.done, 1, nf, on && ok, entry);
+            push(done_end, -1, ng, on && !ok && !retry, item);
+            wave_lds_sync();
+        }
+        nl = again;
+    }
+    // The left piece's values (from the end of their list, as above).
+#pragma unroll 1
+    for (int b = nf; b > 0; b -= 64) {
+        const bool on = b - 1 - lane >= 0;
+        const int entry = W.done[max(b - 1 - lane, 0)];
+        const int item = entry & (kPgItems - 1), k = entry / kPgItems;
+        const double x = pg_left_value(unit_of(W.slot[item]));
+        const bool keep = pg_left_keep(W.env[item & 63].z, x,
+                                       unit_of(second_half(block(item, (uint32_t)k + 1u))));
+        const bool ok = keep && pg_series_clear(x, first_half(block(item, (uint32_t)k + 2u)));
+        wave_lds_sync();
+        if (on)     // not kept: the search goes on with uniform 2 k + 4
+            W.slot[item] = ok ? __builtin_bit_cast(uint64_t, 0.25 * x)
+                              : keep ? 0u : (uint64_t)(2 * k + 4);
+        push(done_end, -1, ng, on && !ok, item);
+        wave_lds_sync();
+    }
+    // The rest, as written.
+    bool fine = true;
+#pragma unroll 1
+    for (int b = 0; b < ng; b += 64) {
+        if (b + lane < ng) {
+            const int item = done_end[-(b + lane)], l = item & 63;
+            double v = 0.0;
+            fine = pg1_draw(W.env[l], a.seed, W.site[l], t, a.instance,
+                            W.j0[l] + (uint32_t)(item >> 6), (uint32_t)W.slot[item], &v) && fine;
+            W.slot[item] = __builtin_bit_cast(uint64_t, v);
+        }
+    }
+    if (!fine)
+        atomicOr(&a.st->status, kStatusGamma);
+    wave_lds_sync();
+    double sum = 0.0;
+    for (int i = 0; i < cnt; ++i)
+        sum += __builtin_bit_cast(double, W.slot[i * 64 + lane]);
     // Segmented inclusive scan over the lanes, segments = runs of one site
     // (lanes past nq form a run of their own and store nothing).
     const int prev = __shfl_up(p, 1, 64), next = __shfl_down(p, 1, 64);
@@ -2643,6 +2821,7 @@ struct gmrf_chain {
     PgEnvelope *d_env = nullptr;
     double *d_psi = nullptr;
     int n_chunks = 0;                 // binomial: PG term chunks of all sites
+    int chunk_terms = kPgFew;         // and the terms of one chunk
     std::vector<int> pass_blocks;     // CSR: blocks per color pass
     uint64_t host_sweeps = 0;         // sweeps enqueued (host view)
     hipStream_t capture_stream = nullptr;
@@ -3155,7 +3334,8 @@ void launch_csr(const gmrf_chain *c, const SweepArgs &a, hipStream_t s, hipEvent
         const int nq = c->n_chunks;
         const int nsite = (int)h.n;
         auto ek = c->model.intercept ? pg_env_kernel<Real, true> : pg_env_kernel<Real, false>;
-        auto tk = c->model.intercept ? pg_chunk_kernel<Real, true> : pg_chunk_kernel<Real, false>;
+        auto tk = c->chunk_terms == kPgMany ? pg_chunk_kernel<kPgMany> : pg_chunk_kernel<kPgFew>;
+        const PgArgs pa{ca.chunk_site, ca.chunk_off, ca.trials, ca.orig, ca.env, ca.chunk_sum};
         const int eb = (nsite + kThreads - 1) / kThreads, tb = (nq + kThreads - 1) / kThreads;
         const int pb = (nsite + kPsiSites - 1) / kPsiSites;
         if (nq > 0) {
@@ -3168,10 +3348,10 @@ void launch_csr(const gmrf_chain *c, const SweepArgs &a, hipStream_t s, hipEvent
         }
         if (nq > 0) {
             if (ev0)
-                hipExtLaunchKernelGGL(tk, dim3(tb), dim3(kThreads), 0, s, ev0, nullptr, 0, ca, a,
+                hipExtLaunchKernelGGL(tk, dim3(tb), dim3(kThreads), 0, s, ev0, nullptr, 0, pa, a,
                                       nq);
             else
-                hipLaunchKernelGGL(tk, dim3(tb), dim3(kThreads), 0, s, ca, a, nq);
+                hipLaunchKernelGGL(tk, dim3(tb), dim3(kThreads), 0, s, pa, a, nq);
             ev0 = nullptr;
         }
         if (ev0)
@@ -3349,7 +3529,7 @@ int upload_trials_layout(gmrf_chain *c, const int32_t *trials, hipStream_t s)
     std::vector<int32_t> buf(n), off(n + 1, 0), site;
     for (int64_t p = 0; p < n; ++p) {
         buf[p] = trials[h.orig_of_slab[p]];
-        off[p + 1] = off[p] + (buf[p] + kPgChunk - 1) / kPgChunk;
+        off[p + 1] = off[p] + (buf[p] + c->chunk_terms - 1) / c->chunk_terms;
     }
     site.resize(std::max<int64_t>(off[n], 1));
     for (int64_t p = 0; p < n; ++p)
@@ -3940,17 +4120,23 @@ size_t gmrf_chain_footprint(const gmrf_graph *g, gmrf_precision p)
     return chain_layout(g, p, nullptr, nullptr, false);
 }
 
-// Number of PG term chunks of a binomial chain (trials in original order).
 // Most PG term chunks of one chain: chunk indices, and the grid of one thread
 // per chunk rounded up to whole blocks, stay within int.
 constexpr int64_t kMaxChunks = INT32_MAX - kThreads;
 
-static int64_t count_chunks(const gmrf_graph *g, const int32_t *trials)
+// Number of PG term chunks of a binomial chain (trials in original order) and
+// the terms of one; what doesn't fit with short chunks is refused.
+static int64_t count_chunks(const gmrf_graph *g, const int32_t *trials, int *terms)
 {
-    int64_t nc = 0;
-    for (int64_t i = 0; i < g->h.n; ++i)
-        nc += (std::max(trials[i], 0) + kPgChunk - 1) / kPgChunk;
-    return nc;
+    int64_t few = 0, many = 0, total = 0;
+    for (int64_t i = 0; i < g->h.n; ++i) {
+        const int m = std::max(trials[i], 0);
+        total += m;
+        few += ((int64_t)m + kPgFew - 1) / kPgFew;
+        many += ((int64_t)m + kPgMany - 1) / kPgMany;
+    }
+    *terms = total >= kPgManyTerms && few <= kMaxChunks ? kPgMany : kPgFew;
+    return *terms == kPgMany ? many : few;
 }
 
 size_t gmrf_binomial_footprint(const gmrf_graph *g, gmrf_precision p, const int32_t *trials)
@@ -3960,7 +4146,8 @@ size_t gmrf_binomial_footprint(const gmrf_graph *g, gmrf_precision p, const int3
         set_error("binomial_footprint: NULL or lattice graph, bad precision or NULL trials");
         return 0;
     }
-    const int64_t nc = count_chunks(g, trials);
+    int terms;
+    const int64_t nc = count_chunks(g, trials, &terms);
     if (nc > kMaxChunks) {
         set_error("binomial_footprint: too many trials in total");
         return 0;
@@ -4042,7 +4229,8 @@ static int chain_create_impl(const char *who, const gmrf_graph *g, const gmrf_mo
         for (int64_t i = 0; i < n; ++i)
             kappa[i] = y[i] - 0.5 * (double)trials[i];
     }
-    const int64_t n_chunks = binomial ? count_chunks(g, trials) : 0;
+    int terms = kPgFew;
+    const int64_t n_chunks = binomial ? count_chunks(g, trials, &terms) : 0;
     if (n_chunks > kMaxChunks)
         return fail(GMRF_E_INVALID_ARG, w + ": too many trials in total");
     const size_t need = chain_layout(g, p, nullptr, nullptr, binomial, n_chunks);
@@ -4059,6 +4247,7 @@ static int chain_create_impl(const char *who, const gmrf_graph *g, const gmrf_mo
     c->binomial = binomial;
     c->lat_tile = is_lattice(g) ? default_tile(g->h) : csr_default_shape(g->h, p, binomial);
     chain_layout(g, p, static_cast<char *>(d_ws), c, binomial, n_chunks);
+    c->chunk_terms = terms;
 
     auto cleanup = [&](int rc) {
         delete c;

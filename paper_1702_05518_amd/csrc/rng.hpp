@@ -351,12 +351,6 @@ struct PgStream {
         blk = draw_words(seed, site, sweep, instance, 0x80000000u | (j << 10) | (u >> 1));
         return open_uniform_f64(blk.w0, blk.w1);
     }
-    __device__ double normal()
-    {
-        const double u1 = next();
-        const double u2 = next();
-        return sqrt_f64(-2.0 * log_open_unit(u1)) * cos_2pi_unit(u2);
-    }
 };
 
 __device__ inline double std_normal_cdf(double x) { return 0.5 * erfc(-x / sqrt(2.0)); }
@@ -399,6 +393,70 @@ struct PgSeries {
     }
 };
 
+// The acceptance of a pair of exponentials in the search of pg_left: E1^2 <=
+// 2 E2 / t for E1 = -log u1, E2 = -log u2.  First from single-precision
+// logarithms (hardware log2): their error is below 1e-6 (1 + e) for every e,
+// so a difference beyond 1e-3 (1 + both sides) decides it as the
+// double-precision test would; only closer calls take the double logarithms.
+// The same decisions, so the same draws, with far fewer double logarithms.
+__device__ __forceinline__ bool pg_pair_ok(double u1, double u2)
+{
+    const float a1 = -kLn2f * __builtin_amdgcn_logf((float)u1);
+    const float a2 = -kLn2f * __builtin_amdgcn_logf((float)u2);
+    const float lhs = a1 * a1, rhs = 2.0f * a2 / (float)kPgT;
+    const float guard = 1e-3f * (1.0f + lhs + rhs);
+    if (lhs - rhs > guard)
+        return false;
+    if (rhs - lhs > guard)
+        return true;
+    const double e1 = -log_open_unit(u1);
+    return !(e1 * e1 > 2.0 * -log_open_unit(u2) / kPgT);
+}
+
+// The left piece's value for an accepted E1 = -log u1.
+__device__ __forceinline__ double pg_left_value(double u1)
+{
+    const double d = 1.0 - kPgT * log_open_unit(u1);
+    return quotient_f64(kPgT, d * d);
+}
+
+// u <= exp(w), w = -z^2 x / 2 in (-0.79, 0]: first against the
+// single-precision exponential (relative error below 1e-6), the double one
+// only within 1e-4 of it.
+__device__ __forceinline__ bool pg_left_keep(double z, double x, double u)
+{
+    const double w = -0.5 * z * z * x;
+    const double ef = (double)__builtin_amdgcn_exp2f((float)w * kLog2ef);
+    if (u < ef * (1.0 - 1e-4))
+        return true;
+    if (u > ef * (1.0 + 1e-4))
+        return false;
+    return u <= exp(w);
+}
+
+// The first test of the series, Y = u a0 <= a0 - a1, is u <= 1 - 3 E^8 (a1 /
+// a0 = 3 E^8 for both forms of the terms), with 3 E^8 below 0.006 here.  From
+// the single-precision exponential (error below 1e-8 absolute at these
+// values) a u more than 1e-5 below it is accepted as the double-precision
+// series would; other u need the series.
+__device__ __forceinline__ bool pg_series_clear(double x, double u)
+{
+    const float xf = (float)x;
+    const float w = x > kPgT ? -kPi2f * xf : -4.0f * __builtin_amdgcn_rcpf(xf);
+    const float q = 3.0f * __builtin_amdgcn_exp2f(w * kLog2ef);
+    return u < 1.0 - (double)q - 1e-5;
+}
+
+// One draw of IG(mu, 1) from its three uniforms (Michael, Schucany & Haas).
+__device__ __forceinline__ double pg_steep_value(double mu, double u1, double u2, double u3)
+{
+    const double nrm = sqrt_f64(-2.0 * log_open_unit(u1)) * cos_2pi_unit(u2);
+    const double y = nrm * nrm;
+    const double my = mu * y;
+    const double x = mu + 0.5 * mu * my - 0.5 * mu * sqrt(4.0 * my + my * my);
+    return u3 > mu / (mu + x) ? mu * mu / x : x;
+}
+
 // IG(1/z, 1) restricted to (0, t).  z < 1/t: the z = 0 law on (0, t) from a
 // normal tail beyond 1/sqrt(t) (1/X = (1 + t E1)^2 / t, E1^2 <= 2 E2 / t),
 // kept with probability exp(-z^2 X / 2).  Otherwise: Michael, Schucany &
@@ -408,61 +466,23 @@ __device__ inline double pg_left(double z, PgStream &s)
     const double t = kPgT;
     if (z < 1.0 / t) {
         for (;;) {
-            double u1, e1 = -1.0;
+            double u1;
             for (;;) {
                 u1 = s.next();
                 const double u2 = s.next();
-                // The test e1^2 > 2 e2 / t first from single-precision
-                // logarithms (hardware log2): their error is below 1e-6 (1 + e)
-                // for every e, so a difference beyond 1e-3 (1 + both sides)
-                // decides it as the double-precision test would; only closer
-                // calls take the double logarithms.  The same decisions, so
-                // the same draws, with far fewer double logarithms.
-                const float a1 = -kLn2f * __builtin_amdgcn_logf((float)u1);
-                const float a2 = -kLn2f * __builtin_amdgcn_logf((float)u2);
-                const float lhs = a1 * a1, rhs = 2.0f * a2 / (float)t;
-                const float guard = 1e-3f * (1.0f + lhs + rhs);
-                bool reject;
-                if (lhs - rhs > guard) {
-                    reject = true;
-                } else if (rhs - lhs > guard) {
-                    reject = false;
-                } else {
-                    e1 = -log_open_unit(u1);
-                    reject = e1 * e1 > 2.0 * -log_open_unit(u2) / t;
-                }
-                if (!reject || s.exhausted)
+                if (pg_pair_ok(u1, u2) || s.exhausted)
                     break;
-                e1 = -1.0;
             }
-            if (e1 < 0.0)
-                e1 = -log_open_unit(u1);
-            const double x = t / ((1.0 + t * e1) * (1.0 + t * e1));
-            // u <= exp(w), w = -z^2 x / 2 in (-0.79, 0]: first against the
-            // single-precision exponential (relative error below 1e-6), the
-            // double one only within 1e-4 of it
-            const double u = s.next();
-            const double w = -0.5 * z * z * x;
-            const double ef = (double)__builtin_amdgcn_exp2f((float)w * kLog2ef);
-            bool keep;
-            if (u < ef * (1.0 - 1e-4))
-                keep = true;
-            else if (u > ef * (1.0 + 1e-4))
-                keep = false;
-            else
-                keep = u <= exp(w);
-            if (keep || s.exhausted)
+            const double x = pg_left_value(u1);
+            if (pg_left_keep(z, x, s.next()) || s.exhausted)
                 return x;
         }
     }
     const double mu = 1.0 / z;
     for (;;) {
-        const double nrm = s.normal();
-        const double y = nrm * nrm;
-        const double my = mu * y;
-        double x = mu + 0.5 * mu * my - 0.5 * mu * sqrt(4.0 * my + my * my);
-        if (s.next() > mu / (mu + x))
-            x = mu * mu / x;
+        const double u1 = s.next();
+        const double u2 = s.next();
+        const double x = pg_steep_value(mu, u1, u2, s.next());
         if (x < t || s.exhausted)
             return x;
     }
@@ -493,34 +513,33 @@ __device__ inline PgEnvelope pg_envelope(double c)
     return e;
 }
 
-// PG(1, c) from the stream of term j; false when the stream ran out.
-__device__ inline bool pg1_draw(const PgEnvelope &e, uint64_t seed, uint32_t site, uint32_t sweep,
-                                uint32_t instance, uint32_t j, double *out)
+// The right piece's value from its uniform.
+__device__ __forceinline__ double pg_right_value(double K, double u)
 {
-    PgStream s{seed, site, sweep, instance, j, 0u, false, Words4{}};
-    for (;;) {
+    return kPgT - quotient_f64(log_open_unit(u), K);
+}
+
+// PG(1, c) from the stream of term j; false when the stream ran out.  used:
+// 0, or the uniforms that a draw of the left piece has taken when it is to go
+// on with its search from the next one.
+__device__ inline bool pg1_draw(const PgEnvelope &e, uint64_t seed, uint32_t site, uint32_t sweep,
+                                uint32_t instance, uint32_t j, uint32_t used, double *out)
+{
+    PgStream s{seed, site, sweep, instance, j, used, false, Words4{}};
+    if (used & 1u)
+        s.blk = draw_words(seed, site, sweep, instance, 0x80000000u | (j << 10) | (used >> 1));
+    for (bool resume = used > 0;; resume = false) {
         double x;
-        if (s.next() < e.right)
-            x = kPgT - log_open_unit(s.next()) / e.K;
+        if (!resume && s.next() < e.right)
+            x = pg_right_value(e.K, s.next());
         else
             x = pg_left(e.z, s);
         const double u = s.next();
         if (s.exhausted)
             return false;
-        // The first test of the series, Y = u a0 <= a0 - a1, is u <= 1 - 3 E^8
-        // (a1 / a0 = 3 E^8 for both forms of the terms), with 3 E^8 below
-        // 0.006 here.  From the single-precision exponential (error below
-        // 1e-8 absolute at these values) a u more than 1e-5 below it is
-        // accepted as the double-precision series would; otherwise the
-        // series runs as written.
-        {
-            const float xf = (float)x;
-            const float w = x > kPgT ? -kPi2f * xf : -4.0f * __builtin_amdgcn_rcpf(xf);
-            const float q = 3.0f * __builtin_amdgcn_exp2f(w * kLog2ef);
-            if (u < 1.0 - (double)q - 1e-5) {
-                *out = 0.25 * x;
-                return true;
-            }
+        if (pg_series_clear(x, u)) {
+            *out = 0.25 * x;
+            return true;
         }
         PgSeries terms(x);
         double S = terms.next();
