@@ -2755,6 +2755,23 @@ __global__ void set_intercept_kernel(DevState *st, double beta0, double n, int b
     st->beta0 = beta0;
 }
 
+// The chain's state block and, with words > 0, the first `words` 4-byte words
+// of its current field (x1: the other parity's buffer, or x0 again) to the
+// caller's host memory.  A few KB in one write-only launch: bound by its own
+// latency.
+__global__ void report_kernel(const DevState *st, const uint32_t *x0, const uint32_t *x1,
+                              long long words, uint32_t *out)
+{
+    constexpr int kHead = (int)(sizeof(DevState) / 4);
+    const uint32_t *h = reinterpret_cast<const uint32_t *>(st);
+    const uint32_t *x = st->sweep & 1ull ? x1 : x0;
+    const long long i0 = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i0 < kHead)
+        out[i0] = h[i0];
+    for (long long i = i0; i < words; i += (long long)gridDim.x * blockDim.x)
+        out[kHead + i] = x[i];
+}
+
 // Posterior mean S1/N and variance (S2 - S1^2/N)/(N - 1), un-permuted to the
 // original site order (orig NULL for a lattice).
 __global__ void stats_kernel(const double *s1, const double *s2, const int *orig, long long n,
@@ -2798,6 +2815,7 @@ struct gmrf_chain {
     const gmrf_graph *g = nullptr;
     gmrf_precision prec = GMRF_FP64;
     gmrf_model model{};
+    int device = -1;            // where the workspace lies (-1: not known)
     uint64_t seed = 0;
     uint32_t instance = 0;
     int64_t rank = 0;
@@ -3453,8 +3471,109 @@ void launch_sweeps(const gmrf_chain *c, const SweepArgs &a, int nsweeps, hipStre
     }
 }
 
+void *current_x(const gmrf_chain *c, uint64_t sweep);
+
+// Pinned host memory that the library's small reads land in: kReportSlots slots
+// of kReportBytes, allocated at the first read and kept for the life of the
+// process (one set for all devices).  A read holds a slot from its launch to
+// the end of its synchronisation; when all are held, or the memory could not
+// be had, the read copies to the caller's memory instead.  A state block and
+// the field of 48 x 40 FP64 sites: two copies to unpinned memory, each with
+// its synchronisation, 44 us; one launch into a slot
+// 19.
+constexpr size_t kReportBytes = 256 << 10;
+constexpr int kReportSlots = 8;
+static_assert(sizeof(DevState) % 8 == 0, "the field follows the state block");
+
+class ReportSlot {
+public:
+    ReportSlot()
+    {
+        std::lock_guard<std::mutex> lock(mu_);
+        if (!tried_) {
+            tried_ = true;
+            void *mem = nullptr;
+            // another thread may be capturing: the allocation is no part of it
+            hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+            if (hipHostMalloc(&mem, kReportSlots * kReportBytes, hipHostMallocPortable) ==
+                hipSuccess)
+                base_ = static_cast<char *>(mem);
+            else
+                (void)hipGetLastError();
+            (void)hipThreadExchangeStreamCaptureMode(&mode);
+        }
+        for (int i = 0; base_ && i < kReportSlots && index_ < 0; ++i)
+            if (!(held_ & 1u << i)) {
+                held_ |= 1u << i;
+                index_ = i;
+            }
+    }
+    ~ReportSlot()
+    {
+        if (index_ < 0)
+            return;
+        std::lock_guard<std::mutex> lock(mu_);
+        held_ &= ~(1u << index_);
+    }
+    ReportSlot(const ReportSlot &) = delete;
+    ReportSlot &operator=(const ReportSlot &) = delete;
+    char *data() const { return index_ < 0 ? nullptr : base_ + index_ * kReportBytes; }
+    // After a failed synchronisation the device may still write: never reused.
+    void keep() { index_ = -1; }
+
+private:
+    int index_ = -1;
+    static inline std::mutex mu_;
+    static inline char *base_ = nullptr;
+    static inline bool tried_ = false;
+    static inline unsigned held_ = 0;
+};
+
+// Reads the state block and, with x, the current field in layout order
+// (nbytes of it) through a slot.  True when it did (*rc the result); false
+// when the general path has to: no free slot, a field too large, or a stream
+// or current device other than the chain's.
+bool read_report(gmrf_chain *c, DevState *out, char *x, size_t nbytes, hipStream_t s, int *rc)
+{
+    int dev = -1;
+    if (c->device < 0 || sizeof(DevState) + nbytes > kReportBytes ||
+        hipGetDevice(&dev) != hipSuccess || dev != c->device)
+        return false;
+    if (s && (hipStreamGetDevice(s, &dev) != hipSuccess || dev != c->device))
+        return false;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (s && (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone))
+        return false;
+    ReportSlot slot;
+    if (!slot.data())
+        return false;
+    const long long words = x ? (long long)(nbytes / 4) : 0;
+    const int blocks = (int)std::min<long long>(std::max<long long>(words / 1024, 1), 32);
+    hipLaunchKernelGGL(report_kernel, dim3(blocks), dim3(kThreads), 0, s, c->d_state,
+                       static_cast<const uint32_t *>(current_x(c, 0)),
+                       static_cast<const uint32_t *>(current_x(c, 1)), words,
+                       reinterpret_cast<uint32_t *>(slot.data()));
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess)
+        e = hipStreamSynchronize(s);
+    if (e != hipSuccess) {
+        slot.keep();
+        *rc = fail(GMRF_E_DEVICE, std::string("state read: ") + hipGetErrorString(e));
+        return true;
+    }
+    std::memcpy(out, slot.data(), sizeof(DevState));
+    if (x)
+        std::memcpy(x, slot.data() + sizeof(DevState), nbytes);
+    *rc = GMRF_OK;
+    return true;
+}
+
 int read_state(gmrf_chain *c, DevState *out, hipStream_t s)
 {
+    int rc;
+    if (read_report(c, out, nullptr, 0, s, &rc))
+        return rc;
     GMRF_HIP(hipMemcpyAsync(out, c->d_state, sizeof(DevState), hipMemcpyDeviceToHost, s));
     GMRF_HIP(hipStreamSynchronize(s));
     return GMRF_OK;
@@ -3499,11 +3618,15 @@ void from_layout(const gmrf_chain *c, const std::vector<char> &buf, double *x)
 int upload_real(const gmrf_chain *c, void *dst, const double *x, hipStream_t s)
 {
     std::vector<char> buf;
-    if (c->prec == GMRF_FP64)
-        to_layout<double>(c, x, buf);
-    else
+    const void *src = x;        // an FP64 lattice's layout is the caller's
+    if (c->prec != GMRF_FP64)
         to_layout<float>(c, x, buf);
-    GMRF_HIP(hipMemcpyAsync(dst, buf.data(), buf.size(), hipMemcpyHostToDevice, s));
+    else if (!is_lattice(c->g))
+        to_layout<double>(c, x, buf);
+    if (!buf.empty())
+        src = buf.data();
+    GMRF_HIP(hipMemcpyAsync(dst, src, real_size(c->prec) * (size_t)c->g->h.n,
+                            hipMemcpyHostToDevice, s));
     GMRF_HIP(hipStreamSynchronize(s));
     return GMRF_OK;
 }
@@ -3557,9 +3680,18 @@ int download_doubles_layout(const gmrf_chain *c, const double *src, double *x, h
 
 bool finite_array(const double *v, int64_t n)
 {
-    for (int64_t i = 0; i < n; ++i)
-        if (!std::isfinite(v[i]))
+    // blocks without an exit inside, so that the tests of a block run in vectors
+    constexpr int64_t kBlock = 4096;
+    for (int64_t b = 0; b < n; b += kBlock) {
+        uint64_t bad = 0;
+        for (int64_t i = b, e = std::min(n, b + kBlock); i < e; ++i) {
+            uint64_t w;
+            std::memcpy(&w, v + i, 8);
+            bad |= (w & 0x7FF0000000000000ull) == 0x7FF0000000000000ull;
+        }
+        if (bad)
             return false;
+    }
     return true;
 }
 
@@ -4270,23 +4402,26 @@ static int chain_create_impl(const char *who, const gmrf_graph *g, const gmrf_mo
                                                               : c->total_slots,
                                                 1),
                            stream);
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(stream);
-    if (e != hipSuccess)
+    if (e == hipSuccess && !x0)
+        e = hipMemsetAsync(c->d_x[0], 0, real_size(p) * (size_t)n, stream);
+    if (e != hipSuccess) {
+        (void)hipStreamSynchronize(stream);     // st is still being read
         return cleanup(fail(GMRF_E_DEVICE, w + ": " + hipGetErrorString(e)));
+    }
+    hipPointerAttribute_t attr{};
+    if (hipPointerGetAttributes(&attr, d_ws) == hipSuccess && attr.type == hipMemoryTypeDevice)
+        c->device = attr.device;
+    else
+        (void)hipGetLastError();
     int rc = upload_real(c, c->d_y, binomial ? kappa.data() : y, stream);
     if (rc == GMRF_OK && binomial)
         rc = upload_trials_layout(c, trials, stream);
-    if (rc != GMRF_OK)
+    if (rc == GMRF_OK && x0)
+        rc = upload_real(c, c->d_x[0], x0, stream);
+    if (rc != GMRF_OK) {
+        (void)hipStreamSynchronize(stream);
         return cleanup(rc);
-    std::vector<double> zeros;
-    if (!x0) {
-        zeros.assign(n, 0.0);
-        x0 = zeros.data();
     }
-    rc = upload_real(c, c->d_x[0], x0, stream);
-    if (rc != GMRF_OK)
-        return cleanup(rc);
     *out = c;
     return GMRF_OK;
 }
@@ -4544,15 +4679,19 @@ int gmrf_get_state(gmrf_chain *c, double *x, double *tau, double *lam, uint64_t 
     if (!c)
         return fail(GMRF_E_INVALID_ARG, "get_state: NULL chain");
     DevState st;
-    int rc = read_state(c, &st, stream);
+    std::vector<char> buf(x ? real_size(c->prec) * (size_t)c->g->h.n : 0);
+    int rc;
+    if (!x || !read_report(c, &st, buf.data(), buf.size(), stream, &rc)) {
+        rc = read_state(c, &st, stream);
+        if (rc == GMRF_OK && x) {
+            GMRF_HIP(hipMemcpyAsync(buf.data(), current_x(c, st.sweep), buf.size(),
+                                    hipMemcpyDeviceToHost, stream));
+            GMRF_HIP(hipStreamSynchronize(stream));
+        }
+    }
     if (rc != GMRF_OK)
         return rc;
     if (x) {
-        const int64_t n = c->g->h.n;
-        std::vector<char> buf(real_size(c->prec) * n);
-        GMRF_HIP(hipMemcpyAsync(buf.data(), current_x(c, st.sweep), buf.size(),
-                                hipMemcpyDeviceToHost, stream));
-        GMRF_HIP(hipStreamSynchronize(stream));
         if (c->prec == GMRF_FP64)
             from_layout<double>(c, buf, x);
         else
