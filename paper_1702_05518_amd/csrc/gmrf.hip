@@ -506,27 +506,34 @@ __device__ __forceinline__ UnitDraws ring_check(const SweepArgs &a, unsigned t, 
     return r.u;
 }
 
-// The wave sums in order, and the draws (after a barrier that follows
-// fold_partials); ends with a barrier.
+// The wave sums in order, and the draws, by the first wavefront (after a
+// barrier that follows fold_partials); valid in lane 0.
+__device__ __forceinline__ HyperIn fold_wave_draws(const SweepArgs &a, unsigned t,
+                                                   const HyperIn &in, const RingUnits &units,
+                                                   bool commit, const FoldLds &L)
+{
+    constexpr int W = kFinishThreads / 64;
+    Red r;
+    r.q = L.red[0];
+    r.sse = L.red[W];
+    r.rsum = L.red[2 * W];
+    for (int w = 1; w < W; ++w) {
+        r.q += L.red[w];
+        r.sse += L.red[W + w];
+        r.rsum += L.red[2 * W + w];
+    }
+    const UnitDraws u = ring_check(a, t, units);
+    return end_of_sweep_draws(a, t, r, in, (int)threadIdx.x & 63, u,
+                              a.dry ? TraceTo{} : trace_of(a), commit);
+}
+
+// The same for every thread of the block; ends with a barrier.
 __device__ __forceinline__ HyperIn fold_draws(const SweepArgs &a, unsigned t, const HyperIn &in,
                                               const RingUnits &units, bool commit, FoldLds &L)
 {
-    constexpr int W = kFinishThreads / 64;
-    const int lane = (int)threadIdx.x & 63, wid = (int)threadIdx.x >> 6;
-    if (wid == 0) {
-        Red r;
-        r.q = L.red[0];
-        r.sse = L.red[W];
-        r.rsum = L.red[2 * W];
-        for (int w = 1; w < W; ++w) {
-            r.q += L.red[w];
-            r.sse += L.red[W + w];
-            r.rsum += L.red[2 * W + w];
-        }
-        const UnitDraws u = ring_check(a, t, units);
-        const HyperIn out = end_of_sweep_draws(a, t, r, in, lane, u,
-                                               a.dry ? TraceTo{} : trace_of(a), commit);
-        if (lane == 0) {
+    if (threadIdx.x < 64) {
+        const HyperIn out = fold_wave_draws(a, t, in, units, commit, L);
+        if (threadIdx.x == 0) {
             L.hyp[0] = out.tau;
             L.hyp[1] = out.lam;
             L.hyp[2] = out.beta0;
@@ -1289,23 +1296,42 @@ __device__ __forceinline__ int xcd_tile(int b, int nb)
     return x * per + min(x, rem) + (b >> 3);
 }
 
-// The scalars of a sweep's site updates from the state it runs with.
+// The scalars of a sweep's site updates, in LDS: written by the first
+// wavefront from the state the sweep runs with, read by all after a barrier.
+template <typename Real, int ST> struct SweepScalars {
+    double beta0;
+    Real tau, lam, tau_rho;
+    Real qtab[2 * (ST + 1)];
+};
+
+template <typename Real, int ST>
+__device__ __forceinline__ void put_scalars(SweepScalars<Real, ST> &S, const SweepArgs &a,
+                                            const HyperIn &in)
+{
+    qtab_fill<Real, ST>(S.qtab, (Real)in.tau, (Real)in.lam);
+    if (threadIdx.x == 0) {
+        S.beta0 = in.beta0;
+        S.tau = (Real)in.tau;
+        S.lam = (Real)in.lam;
+        S.tau_rho = (Real)(in.tau * a.rho);
+    }
+}
+
 template <typename Real, int ST, bool B0>
-__device__ __forceinline__ SiteCtx<Real> site_ctx(const SweepArgs &a, const HyperIn &in,
-                                                  const Real *qtab)
+__device__ __forceinline__ SiteCtx<Real> site_ctx(const SweepArgs &a,
+                                                  const SweepScalars<Real, ST> &S)
 {
     SiteCtx<Real> sc;
-    sc.tau = uniform_value((Real)in.tau);
-    sc.lam = uniform_value((Real)in.lam);
-    sc.tau_rho = uniform_value((Real)(in.tau * a.rho));
-    site_scales<Real>(sc.tau, sc.lam, ST, sc.inv_q_full, sc.isd_full);
-    sc.inv_q_full = uniform_value(sc.inv_q_full);
-    sc.isd_full = uniform_value(sc.isd_full);
-    sc.beta0 = B0 ? uniform_value(in.beta0) : 0.0;
-    sc.beta0_r = B0 ? uniform_value((Real)in.beta0) : (Real)0;
+    sc.tau = uniform_value(S.tau);
+    sc.lam = uniform_value(S.lam);
+    sc.tau_rho = uniform_value(S.tau_rho);
+    sc.inv_q_full = uniform_value(S.qtab[ST]);
+    sc.isd_full = uniform_value(S.qtab[2 * ST + 1]);
+    sc.beta0 = B0 ? uniform_value(S.beta0) : 0.0;
+    sc.beta0_r = B0 ? (Real)sc.beta0 : (Real)0;
     sc.one_minus_rho = a.one_minus_rho;
     sc.rho = a.rho;
-    sc.qtab = qtab;
+    sc.qtab = S.qtab;
     return sc;
 }
 
@@ -1420,7 +1446,8 @@ __device__ __forceinline__ void write_quads(const Real (&x)[Cfg::NQ][4], Real *_
 // halo inside the lattice; the general path also takes tiles cut by its edge).
 template <typename Real, typename Cfg, bool INTERIOR, bool B0, bool V2>
 __device__ __forceinline__ void lattice_tile(Real *xs, const LatArgs<Real> &la, const SweepArgs &a,
-                                             const TileAt &at, const SiteCtx<Real> &sc,
+                                             const TileAt &at,
+                                             const SweepScalars<Real, Cfg::ST> &S,
                                              const unsigned t, const int tile, const int rel,
                                              const AccPlan &plan)
 {
@@ -1441,6 +1468,7 @@ __device__ __forceinline__ void lattice_tile(Real *xs, const LatArgs<Real> &la, 
         stage_tile<Real, Cfg>(xs, q, ring);
     }
     lds_barrier();
+    const SiteCtx<Real> sc = site_ctx<Real, Cfg::ST, B0>(a, S);
     const Red rd = lattice_phases<Real, Cfg, INTERIOR, B0, true>(xs, q, at, sc, [&](auto J) {
         constexpr int j = decltype(J)::value;
         if constexpr (!kYAhead<Real, Cfg>) {
@@ -1465,7 +1493,13 @@ __device__ __forceinline__ void lattice_tile(Real *xs, const LatArgs<Real> &la, 
 // tau, lam, beta0, identically in every block; the tile loads wait, since
 // every load of the fold's chain would otherwise wait for them too: 2048 x
 // 2048 FP32 40.5 instead of 32.5 us), and the block of tile 0 records the
-// draws for the next sweep kernel and the commit.  Without fold the sweep
+// draws for the next sweep kernel and the commit.  The draws and the sweep's
+// scalars are the first wavefront's; the other wavefronts go on to their tile
+// and read them after the barrier that publishes it (against two barriers and
+// every wavefront deriving the scalars: 512 x 512 FP64 9.6 -> 9.3 us, 1024 x
+// 1000 4-neighbour FP64 15.1 -> 14.7, 2048 x 2048 FP32 / FP64 31.0 / 44.0 ->
+// 30.8 / 43.5; the tile's loads before the draws, in one kernel with them,
+// spill: 37.2 / 47.1).  Without fold the sweep
 // runs with the committed state (the first sweep of a call, and timing runs).
 // V2: the chain draws its site normals by the paired contract
 // (lattice_normal).
@@ -1482,28 +1516,39 @@ __device__ __forceinline__ void lattice_sweep_block(const LatArgs<Real> &la, con
                                                     const AccPlan plan)
 {
     __shared__ __align__(16) Real xs[Cfg::LH * Cfg::LW];
-    __shared__ Real qtab[2 * (Cfg::ST + 1)];
+    __shared__ SweepScalars<Real, Cfg::ST> S;
+    __shared__ FoldLds L;
+    static_assert(Cfg::NT >= kFinishThreads, "the finish needs kFinishThreads threads");
 
     const unsigned t = (unsigned)(a.st->sweep + (unsigned long long)rel);
-    HyperIn hin;
+    const HyperIn in = inputs_of(a, fold ? rel - 1 : 0);
+    SweepArgs fa = a;
+    fa.dry = a.dry || tile != 0;          // one block stores the reductions and the trace
+    RingUnits units{{0.0, 0.0, false}, 0ull, 0u};
+    if (fold)
+        units = ring_ahead(a, rel);
     if (fold) {
-        SweepArgs fa = a;
-        fa.dry = a.dry || tile != 0;      // one block stores the reductions and the trace
-        hin = end_sweep_block<Cfg::NT>(fa, partials_of(a, rel - 1), t - 1u, inputs_of(a, rel - 1),
-                                       ring_ahead(a, rel), false);
-        if (!fa.dry && threadIdx.x == 0) {
-            double *const h = a.st->hs[rel & 1];
-            h[0] = hin.tau;
-            h[1] = hin.lam;
-            h[2] = hin.beta0;
-        }
-    } else {
-        hin = inputs_of(a, 0);
+        fold_partials<4>(fa, partials_of(a, rel - 1), L, [] {});
+        lds_barrier();
     }
-    if (B0 && plan.out >= 0 && tile == 0 && threadIdx.x == 0 && !a.dry)
-        a.st->deferred_b0[plan.out] = hin.beta0;
-    const SiteCtx<Real> sc = site_ctx<Real, Cfg::ST, B0>(a, hin, qtab);
-    qtab_fill<Real, Cfg::ST>(qtab, sc.tau, sc.lam);
+    if (threadIdx.x < 64) {
+        HyperIn hin = in;
+        if (fold) {
+            hin = fold_wave_draws(fa, t - 1u, in, units, false, L);
+            hin.tau = uniform_value(hin.tau);
+            hin.lam = uniform_value(hin.lam);
+            hin.beta0 = uniform_value(hin.beta0);
+            if (!fa.dry && threadIdx.x == 0) {
+                double *const h = a.st->hs[rel & 1];
+                h[0] = hin.tau;
+                h[1] = hin.lam;
+                h[2] = hin.beta0;
+            }
+        }
+        if (B0 && plan.out >= 0 && !fa.dry && threadIdx.x == 0)
+            a.st->deferred_b0[plan.out] = hin.beta0;
+        put_scalars<Real, Cfg::ST>(S, a, hin);
+    }
     const int tr = tile / la.tiles_c, tc = tile - tr * la.tiles_c;
     const TileAt at{tr * Cfg::TH, tc * Cfg::TW, la.rows, la.cols};
     const int interior = at.r0 >= Cfg::RB && at.c0 >= Cfg::CB &&
@@ -1511,9 +1556,9 @@ __device__ __forceinline__ void lattice_sweep_block(const LatArgs<Real> &la, con
                          at.c0 + Cfg::TW + Cfg::CA <= at.cols && at.cols <= kOffsetCols;
     // two paths to the end, so that neither's registers live across the other
     if (__builtin_amdgcn_readfirstlane(interior))
-        lattice_tile<Real, Cfg, true, B0, V2>(xs, la, a, at, sc, t, tile, rel, plan);
+        lattice_tile<Real, Cfg, true, B0, V2>(xs, la, a, at, S, t, tile, rel, plan);
     else
-        lattice_tile<Real, Cfg, false, B0, V2>(xs, la, a, at, sc, t, tile, rel, plan);
+        lattice_tile<Real, Cfg, false, B0, V2>(xs, la, a, at, S, t, tile, rel, plan);
 }
 
 template <typename Real, typename Cfg, bool B0, bool V2>
