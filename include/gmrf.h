@@ -385,7 +385,10 @@ int gmrf_set_trace(gmrf_chain *c, double *d_trace, int64_t capacity, hipStream_t
  * bytes, at most 32 colors) runs the color passes and the draws in one
  * 512-thread block with the field in LDS -- all the sweeps of a call in one
  * launch, or, for the binomial model, one sweep per launch after the
- * Polya-Gamma launches.  Shape 2 gives bitwise the results of shape 0;
+ * Polya-Gamma launches.  A new binomial chain on a graph with chunk tables
+ * (as for shape 1, with 8 bytes more per site of R) runs its color passes as
+ * one chunked launch until gmrf_chain_set_tile sets shape 0 or 2 (its results
+ * agree with theirs to rounding).  Shape 2 gives bitwise the results of shape 0;
  * shape 1 computes each site's draw the same way but groups the FP64
  * reductions by chunk, so its chains agree with the others to rounding.  A
  * new

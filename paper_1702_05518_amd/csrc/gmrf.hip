@@ -1787,6 +1787,7 @@ template <typename Real> struct CsrArgs {
     double *chunk_sum;          // binomial: run sums of the PG(1, .) terms (see below)
     PgEnvelope *env;            // binomial: each site's PG envelope for the current sweep
     double *psi;                // binomial: each site's psi for the current sweep
+    Real *old;                  // binomial, chunked: the field as the sweep found it (else NULL)
 };
 
 // One site per thread.  The first NB neighbours are gathered in one batch
@@ -1832,6 +1833,29 @@ __device__ __forceinline__ CsrScalars csr_scalars(const SweepArgs &a, bool b0)
     v.t = (unsigned)a.st->sweep;
     v.acc = (long long)v.t >= a.burn_in;
     return v;
+}
+
+// The binomial model's update of a site (Sec. 3.2): 1/Qii and Qii^-1/2 with
+// Qii = tau D_ii + psi_i, and the draw from its neighbour sum s.
+template <typename Real>
+__device__ __forceinline__ void binomial_scales(Real tau, int deg, double psi, Real &inv_q,
+                                                Real &isd)
+{
+    const Real Q = fma(tau, (Real)deg, (Real)psi);
+    if constexpr (sizeof(Real) == 8) {
+        inv_q = 1.0 / Q;
+        isd = 1.0 / sqrt(Q);
+    } else {
+        inv_q = 1.0f / Q;
+        isd = __builtin_amdgcn_rsqf(Q);
+    }
+}
+template <typename Real>
+__device__ __forceinline__ Real binomial_draw(Real kappa, double psi, double beta0, Real s, Real z,
+                                              Real tau_rho, Real inv_q, Real isd)
+{
+    const Real beff = (Real)((double)kappa - psi * beta0);
+    return fma(z, isd, fma(tau_rho, s, beff) * inv_q);
 }
 
 // Site p (slab position) of the color slab starting at lo: the update of
@@ -1882,17 +1906,9 @@ __device__ __forceinline__ void csr_site(const CsrArgs<Real> &ca, const SweepArg
     const Real z = site_normal<Real>(draw_words(a.seed, id, v.t, a.instance, 0u));
     Real xn;
     if constexpr (BIN) {
-        const Real Q = fma(tau, (Real)deg, (Real)psi);
         Real inv_q, isd;
-        if constexpr (sizeof(Real) == 8) {
-            inv_q = 1.0 / Q;
-            isd = 1.0 / sqrt(Q);
-        } else {
-            inv_q = 1.0f / Q;
-            isd = __builtin_amdgcn_rsqf(Q);
-        }
-        const Real beff = (Real)((double)yv - psi * v.beta0);
-        xn = fma(z, isd, fma(tau_rho, s, beff) * inv_q);
+        binomial_scales<Real>(tau, deg, psi, inv_q, isd);
+        xn = binomial_draw<Real>(yv, psi, v.beta0, s, z, tau_rho, inv_q, isd);
     } else {
         const Real lam = (Real)v.lam;
         Real inv_q, isd;
@@ -2027,7 +2043,8 @@ template <typename Real> struct FusedArgs {
     const uint2 *loc_grp;                            // their neighbours, four per group
     const unsigned *loc_id;                          // original id of each staged site
     Real *x0, *x1;                                   // ping-pong state, slab order
-    const Real *y;                                   // y (slab order)
+    const Real *y;                                   // y or kappa (slab order)
+    const double *psi;                               // binomial: psi of the sweep (slab order)
     int k;                                           // colors
 };
 
@@ -2052,6 +2069,7 @@ template <typename Real> struct FusedRow {
     uint2 g[kRowGroups];
     unsigned head;
     Real y, z, inv_q, isd;
+    double psi;                 // binomial
 };
 
 // Neighbour j of a group: the byte offset of its value in LDS.
@@ -2078,7 +2096,13 @@ __device__ __forceinline__ bool row_below(uint2 g, int j, unsigned lo4)
 // original id and sweep only) go to LDS; the fold's draws; the color phases
 // run in LDS, each owned site's q / sse terms, accumulators and write-back
 // taken as it is drawn.
-template <typename Real, bool B0>
+//
+// BIN: the binomial model (the update of csr_site, psi drawn beforehand).  A
+// sweep reads x1, where the envelope kernel copied the field, and writes x0:
+// the field lies in x0 between sweeps, as for the color passes, which this
+// replaces (a sweep of 14,926 sites, seven colors and 5.1 million trials: FP64
+// 114 -> 90 us, FP32 112 -> 90).
+template <typename Real, bool B0, bool BIN = false>
 __device__ __forceinline__ void csr_fused_block(const FusedArgs<Real> &fa, const SweepArgs &a,
                                                 const int b, const int rel, const int fold)
 {
@@ -2088,8 +2112,8 @@ __device__ __forceinline__ void csr_fused_block(const FusedArgs<Real> &fa, const
     __shared__ FoldLds fl;
 
     const unsigned t = (unsigned)(a.st->sweep + (unsigned long long)rel);
-    const Real *src = (t & 1u) ? fa.x1 : fa.x0;
-    Real *dst = (t & 1u) ? fa.x0 : fa.x1;
+    const Real *src = BIN || (t & 1u) ? fa.x1 : fa.x0;
+    Real *dst = BIN || (t & 1u) ? fa.x0 : fa.x1;
     const int k = fa.k;
     const int *meta = fa.ch_meta + (size_t)b * (3 * k + 1);
     const int loc0 = fa.ch_loc[b], nloc = fa.ch_loc[b + 1] - loc0;
@@ -2110,6 +2134,7 @@ __device__ __forceinline__ void csr_fused_block(const FusedArgs<Real> &fa, const
     unsigned *lhead = reinterpret_cast<unsigned *>(fused_lds + off);
     off += lds_align16(sizeof(unsigned) * (size_t)nr);
     uint2 *lgrp = reinterpret_cast<uint2 *>(fused_lds + off);
+    double *ps = reinterpret_cast<double *>(fused_lds + off + 8 * (size_t)ngrp);   // BIN: psi
     for (int i = (int)threadIdx.x; i < 3 * k + 1; i += kThreads)
         sm[i] = meta[i];
 
@@ -2148,10 +2173,13 @@ __device__ __forceinline__ void csr_fused_block(const FusedArgs<Real> &fa, const
         if (first && fold)
             fold_partials<kFoldUnroll>(a, partials_of(a, rel - 1), fl, [] {});
         Real xv[kFusedCH], yv[kFusedCH];
+        double pv[kFusedCH];
 #pragma unroll
         for (int j = 0; j < kFusedCH; ++j) {
             xv[j] = src[p[j]];
             yv[j] = fa.y[p[j]];
+            if constexpr (BIN)
+                pv[j] = fa.psi[p[j]];
         }
         if constexpr (sizeof(Real) == 4) {
             // FP32: the batch's variates while its gathers are in flight (the
@@ -2170,6 +2198,9 @@ __device__ __forceinline__ void csr_fused_block(const FusedArgs<Real> &fa, const
                 xs[s] = xv[j];
             if (s < nr)
                 ys[s] = yv[j];
+            if constexpr (BIN)
+                if (s < nr)
+                    ps[s] = pv[j];
         }
     };
     RingUnits units{};
@@ -2201,7 +2232,7 @@ __device__ __forceinline__ void csr_fused_block(const FusedArgs<Real> &fa, const
     const Real tau = (Real)hin.tau, lam = (Real)hin.lam, tau_rho = (Real)(hin.tau * a.rho);
     const double beta0 = B0 ? hin.beta0 : 0.0;
     const bool acc = (long long)t >= a.burn_in;
-    if (threadIdx.x < kQtabDeg)
+    if (!BIN && threadIdx.x < kQtabDeg)
         site_scales<Real>(tau, lam, (int)threadIdx.x, qtab[threadIdx.x],
                           qtab[kQtabDeg + threadIdx.x]);
     lds_barrier();
@@ -2224,7 +2255,10 @@ __device__ __forceinline__ void csr_fused_block(const FusedArgs<Real> &fa, const
             r.g[j] = lgrp[4 * j < deg ? first + j : 0];
         r.y = ys[s];
         r.z = zs[s];
-        if (deg < kQtabDeg) {
+        if constexpr (BIN) {
+            r.psi = ps[s];
+            binomial_scales<Real>(tau, deg, r.psi, r.inv_q, r.isd);
+        } else if (deg < kQtabDeg) {
             r.inv_q = qtab[deg];
             r.isd = qtab[kQtabDeg + deg];
         } else {
@@ -2260,8 +2294,14 @@ __device__ __forceinline__ void csr_fused_block(const FusedArgs<Real> &fa, const
                 for (int j = 0; j < 4; ++j)
                     sum += value(g, j);
             }
-            const Real yeff = B0 ? row.y - (Real)beta0 : row.y;
-            const Real xn = site_draw<Real>(yeff, sum, row.z, lam, tau_rho, row.inv_q, row.isd);
+            Real xn;
+            if constexpr (BIN) {
+                xn = binomial_draw<Real>(row.y, row.psi, beta0, sum, row.z, tau_rho, row.inv_q,
+                                         row.isd);
+            } else {
+                const Real yeff = B0 ? row.y - (Real)beta0 : row.y;
+                xn = site_draw<Real>(yeff, sum, row.z, lam, tau_rho, row.inv_q, row.isd);
+            }
             xs[s] = xn;
             const int o = s - lo;
             if (o < own) {
@@ -2285,10 +2325,15 @@ __device__ __forceinline__ void csr_fused_block(const FusedArgs<Real> &fa, const
                         }
                 }
                 rd.q += (1.0 - a.rho) * (double)deg * xd * xd + a.rho * edge;
-                const double rr = B0 ? (double)row.y - beta0 - xd : (double)row.y - xd;
-                rd.sse += rr * rr;
-                if (B0)
-                    rd.rsum += rr;
+                if constexpr (BIN) {
+                    rd.sse += row.psi;
+                    rd.rsum += (double)row.y - row.psi * xd;
+                } else {
+                    const double rr = B0 ? (double)row.y - beta0 - xd : (double)row.y - xd;
+                    rd.sse += rr * rr;
+                    if (B0)
+                        rd.rsum += rr;
+                }
                 if (acc) {
                     const double phi = B0 ? xd + beta0 : xd;
                     unsafeAtomicAdd(a.s1 + pos, phi);
@@ -2307,11 +2352,11 @@ __device__ __forceinline__ void csr_fused_block(const FusedArgs<Real> &fa, const
 
 // Block b takes chunk xcd_tile(b): each XCD sweeps a contiguous run of
 // chunks, which the locality order makes a compact region.
-template <typename Real, bool B0>
+template <typename Real, bool B0, bool BIN>
 __global__ __launch_bounds__(kThreads) void csr_fused_kernel(FusedArgs<Real> fa, SweepArgs a,
                                                              int rel, int fold)
 {
-    csr_fused_block<Real, B0>(fa, a, xcd_tile((int)blockIdx.x, (int)gridDim.x), rel, fold);
+    csr_fused_block<Real, B0, BIN>(fa, a, xcd_tile((int)blockIdx.x, (int)gridDim.x), rel, fold);
 }
 
 // Batched form: one entry per block over the chunks of every chunked
@@ -2474,7 +2519,7 @@ __global__ __launch_bounds__(kCsrPersistThreads) void csr_persistent_kernel(CsrA
 
 // ---------------------------------------------------------------------------
 // general graphs, binomial logit model (Sec. 3.2 with Polya-Gamma
-// augmentation): two launches per color
+// augmentation)
 // ---------------------------------------------------------------------------
 // psi_p ~ PG(m_p, beta0 + x_p) is the sum of m_p PG(1, .) terms.  Every
 // psi_p of a sweep depends only on beta0 and site p's value at the start of
@@ -2490,7 +2535,8 @@ __global__ __launch_bounds__(kCsrPersistThreads) void csr_persistent_kernel(CsrA
 //   * the psi kernel, one wavefront per site: psi_p is the sum of the site's
 //     run sums (at most m_p / (64 kPgFew) + 2 of them), lane l taking runs
 //     l, l + 64, ... and a fixed tree joining the lanes.
-// Each color pass then runs one thread per site: x_p ~ N(m, 1/Q) with
+// The color passes then run (as one chunked launch, one launch each, or in one
+// block) with x_p ~ N(m, 1/Q) with
 // Q = tau D_pp + psi_p, m = (kappa_p - psi_p beta0 + tau rho sum_{j~p} x_j) / Q.
 constexpr int kPsiSites = kThreads / 64;        // sites per block of the psi kernel
 
@@ -2551,7 +2597,10 @@ __global__ __launch_bounds__(kThreads) void pg_env_kernel(CsrArgs<Real> ca, Swee
     if (p >= lo + cnt)
         return;
     const double b0 = B0 ? a.st->beta0 : 0.0;
-    ca.env[p] = pg_envelope(b0 + (double)ca.x[p]);
+    const Real x = ca.x[p];
+    if (ca.old)
+        ca.old[p] = x;
+    ca.env[p] = pg_envelope(b0 + (double)x);
 }
 
 // Chunks 0 .. nq - 1; the grid is whole blocks of whole wavefronts, so chunk
@@ -2885,6 +2934,7 @@ struct gmrf_chain {
     double *d_psi = nullptr;
     int n_chunks = 0;                 // binomial: PG term chunks of all sites
     int chunk_terms = kPgFew;         // and the terms of one chunk
+    bool bin_chunked = false;         // binomial: the color passes as one chunked launch
     std::vector<int> pass_blocks;     // CSR: blocks per color pass
     uint64_t host_sweeps = 0;         // sweeps enqueued (host view)
     hipStream_t capture_stream = nullptr;
@@ -3153,6 +3203,7 @@ template <typename Real> CsrArgs<Real> csr_args(const gmrf_chain *c)
     ca.chunk_sum = c->d_chunk_sum;
     ca.env = c->d_env;
     ca.psi = c->d_psi;
+    ca.old = c->bin_chunked ? static_cast<Real *>(c->d_x[1]) : nullptr;
     return ca;
 }
 
@@ -3280,11 +3331,23 @@ bool csr_persist_fits(const HostGraph &h, gmrf_precision p)
 
 // Can the chunked one-launch sweep take this chain?  (Its graph's chunks fit
 // the LDS and index limits; not the binomial model, whose Polya-Gamma draws
-// run per site before the color passes.)
+// come between the sweeps: see binomial_chunks_fit.)
 bool csr_fused_fits(const HostGraph &h, gmrf_precision p, bool binomial)
 {
     return h.stencil == 0 && h.chunks_ok && !binomial &&
            (p == GMRF_FP64 ? h.max_lds8 : h.max_lds4) <= kFusedLaunchLds;
+}
+
+// Can a binomial chain's color passes run as one chunked launch?  When the
+// chunks and their psi fit, and the envelope kernel runs (it copies the field
+// that the launch reads).  A new chain then does, until a shape is set: FP64
+// sweeps, chunked / one block / color passes, of 500 sites 29.6 / 34.0 / 40.8
+// us, 2,000 34.0 / 43.0 / 50.2, 4,000 38.1 / 57.3 / 56.7, 14,926 (8 times the
+// trials) 90 / - / 114.
+bool binomial_chunks_fit(const HostGraph &h, gmrf_precision p, int64_t n_chunks)
+{
+    return n_chunks > 0 && csr_fused_fits(h, p, false) &&
+           (p == GMRF_FP64 ? h.max_lds8 : h.max_lds4) + 8 * h.max_r <= kFusedLaunchLds;
 }
 
 // Default shape of a general-graph chain: the one block while it covers
@@ -3311,7 +3374,7 @@ int csr_default_shape(const HostGraph &h, gmrf_precision p, bool binomial)
 // Partial slots of one sweep of a general-graph chain in shape k.
 int csr_slots(const gmrf_chain *c, int k)
 {
-    if (k == kFused)
+    if (k == kFused || c->bin_chunked)
         return c->g->h.nchunks;
     int slots = 0;
     for (int nb : c->pass_blocks)
@@ -3325,7 +3388,10 @@ bool is_persistent(const gmrf_chain *c) { return c->lat_tile == kPersistent && !
 
 // Does the chain draw the hyperparameters inside its sweep kernel (no commit
 // kernel)?
-bool draws_in_sweep(const gmrf_chain *c) { return c->lat_tile == kPersistent; }
+bool draws_in_sweep(const gmrf_chain *c)
+{
+    return c->lat_tile == kPersistent && !c->bin_chunked;
+}
 
 // Launch configuration of the small element-wise kernels.
 int elementwise_blocks(int64_t n)
@@ -3352,6 +3418,7 @@ template <typename Real> FusedArgs<Real> fused_args(const gmrf_chain *c, bool sw
     fa.x0 = static_cast<Real *>(c->d_x[swap ? 1 : 0]);
     fa.x1 = static_cast<Real *>(c->d_x[swap ? 0 : 1]);
     fa.y = static_cast<const Real *>(c->d_y);
+    fa.psi = c->d_psi;
     fa.k = g->h.k;
     return fa;
 }
@@ -3368,8 +3435,11 @@ void launch_fused(const gmrf_chain *c, const FusedArgs<Real> &fa, const SweepArg
                   hipStream_t s, hipEvent_t ev0, hipEvent_t ev1, int rel, int fold)
 {
     const HostGraph &h = c->g->h;
-    auto kern = c->model.intercept ? csr_fused_kernel<Real, true> : csr_fused_kernel<Real, false>;
-    const size_t lds = fused_lds_bytes<Real>(h);
+    const bool b0 = c->model.intercept, bin = c->binomial;
+    auto kern = bin ? (b0 ? csr_fused_kernel<Real, true, true> : csr_fused_kernel<Real, false, true>)
+                    : (b0 ? csr_fused_kernel<Real, true, false>
+                          : csr_fused_kernel<Real, false, false>);
+    const size_t lds = fused_lds_bytes<Real>(h) + (bin ? 8 * (size_t)h.max_r : 0);
     if (ev0 || ev1)
         hipExtLaunchKernelGGL(kern, dim3(h.nchunks), dim3(kThreads), lds, s, ev0, ev1, 0, fa, a,
                               rel, fold);
@@ -3423,6 +3493,10 @@ void launch_csr(const gmrf_chain *c, const SweepArgs &a, hipStream_t s, hipEvent
         else
             hipLaunchKernelGGL(pg_psi_kernel<Real>, dim3(pb), dim3(kThreads), 0, s, ca, 0, nsite);
         ev0 = nullptr;
+        if (c->bin_chunked) {
+            launch_fused<Real>(c, fused_args<Real>(c), a, s, nullptr, ev1, 0, 0);
+            return;
+        }
         if (c->lat_tile == kPersistent) {       // the color passes and draws in one block
             launch_csr_persistent<Real>(c, a, 1, s, ev0, ev1);
             return;
@@ -4422,9 +4496,13 @@ static int chain_create_impl(const char *who, const gmrf_graph *g, const gmrf_mo
     c->instance = instance;
     c->rank = rank;
     c->binomial = binomial;
+    c->n_chunks = (int)n_chunks;
     c->lat_tile = is_lattice(g) ? default_tile(g->h) : csr_default_shape(g->h, p, binomial);
+    c->bin_chunked = binomial && binomial_chunks_fit(g->h, p, n_chunks);
     chain_layout(g, p, static_cast<char *>(d_ws), c, binomial, n_chunks);
     c->chunk_terms = terms;
+    if (!is_lattice(g))
+        c->total_slots = csr_slots(c, c->lat_tile);
 
     auto cleanup = [&](int rc) {
         delete c;
@@ -4896,7 +4974,7 @@ int gmrf_chain_set_tile(gmrf_chain *c, int32_t tile)
                                             "shape 1 when its chunks fit (not for the binomial "
                                             "model); shape 2 when its field fits in LDS (at most "
                                             "122880 bytes of state) and it has at most 32 colors");
-        if (tile != c->lat_tile) {
+        if (tile != c->lat_tile || c->bin_chunked) {
             // shape 1 keeps x in buffer (sweep & 1), the others in buffer 0:
             // move it when the chain has run an odd number of sweeps
             if ((tile == kFused) != (c->lat_tile == kFused) && (c->host_sweeps & 1u)) {
@@ -4907,6 +4985,7 @@ int gmrf_chain_set_tile(gmrf_chain *c, int32_t tile)
                              : hipMemcpy(c->d_x[0], c->d_x[1], bytes, hipMemcpyDeviceToDevice));
             }
             c->lat_tile = tile;
+            c->bin_chunked = false;
             c->total_slots = csr_slots(c, tile);
             drop_graphs(c);
         }
