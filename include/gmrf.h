@@ -464,7 +464,9 @@ int gmrf_batch_create(gmrf_chain *const *chains, int32_t count, void *d_ws, size
 int gmrf_batch_destroy(gmrf_batch *b);
 
 /* nsweeps sweeps of every chain of the batch; flags as for gmrf_sweep
- * (GMRF_WITH_HYPER, GMRF_CAPTURE). */
+ * (GMRF_WITH_HYPER, GMRF_CAPTURE).  A batch of lattices and graphs runs a
+ * longer call's graph launches on a stream of its own, which starts after the
+ * work already on `stream` and which `stream` waits for. */
 int gmrf_batch_sweep(gmrf_batch *b, int32_t nsweeps, uint32_t flags, hipStream_t stream);
 
 /* Choose the tile shape of the batch's lattice chains for the shared launch:
