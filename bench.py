@@ -35,15 +35,18 @@ BIG = 8192
 STENCIL = 8
 HBM_PEAK_GBS = 8000.0
 # algorithmic bytes per site update, accumulating sweeps: lattice x read + x
-# write + y read + S1 / S2 read-modify-write; a general graph adds its CSR
-# row (row offset + column indices at mean degree ~6) and the slab-to-id map
-BYTES_PER_SITE = {"fp32_acc": 44, "fp64_acc": 56}
+# write + y read + its share of the S1 / S2 read-modify-write and of the fields
+# read back for it, once per five FP32 sweeps (12 + (32 + 16) / 5) or three
+# FP64 sweeps (24 + (32 + 16) / 3); a general graph has x, y, S1 / S2 in every
+# sweep, its CSR row (row offset + column indices at mean degree ~6) and the
+# slab-to-id map
+BYTES_PER_SITE = {"fp32_acc": 21.6, "fp64_acc": 40}
 GRAPH_PROBE_SITES = 1_000_000       # sites of the Delaunay counter probe
 BURN_IN_BYTES_PER_SITE = 12          # FP32 burn-in sweep: x read + x write + y read
 CSR_BYTES_PER_SITE = {"fp32_acc": 72, "fp64_acc": 84}
 METRIC = ("site-updates/s + HBM GB/s fraction per sweep; p50/p99 solve latency "
           "(FP32 vs FP64)")
-SWEEP_KERNEL = "lattice_sweep_kernel<float, LatCfg<8, 64, 64, 512, 4>, false, false>"
+SWEEP_KERNEL = "lattice_sweep_kernel<float, LatCfg<8, 64, 64, 512>, false, false>"
 # rocprofv3 summaries of the dominant kernel (committed under profiles/):
 # its average duration in the kernel trace of this benchmark's command, and
 # its HBM traffic per launch from FETCH_SIZE / WRITE_SIZE scaled by a device
@@ -115,7 +118,7 @@ def trace_summary(trace_csv, commands):
         groups.setdefault((r["Kernel_Name"], blocks, wg), []).append(d)
     rows = sorted(groups.items(), key=lambda kv: -sum(kv[1]))
     out = ["# Kernel trace: " + commands[0].split(" -- ", 1)[-1], "",
-           "Commands (from the repository root on the GPU box):", "", "```", *commands, "```", "",
+           "Commands (from the repository root):", "", "```", *commands, "```", "",
            "Per kernel and launch size (workgroups x threads), durations in ns:", "",
            "| Kernel | Workgroups x threads | Calls | Average | Min | Max | % of GPU time |",
            "|---|---|---|---|---|---|---|"]
@@ -158,7 +161,7 @@ def traffic_summary(fetch_csv, write_csv, dram_csv, side, commands):
     n = side * side
     alg = BYTES_PER_SITE["fp32_acc"] * n
     out = [f"# HBM traffic counters: FP32 lattice sweep kernel, {side}x{side}, 8 neighbours", "",
-           "Commands (from the repository root on the GPU box):", "", "```", *commands, "```", "",
+           "Commands (from the repository root):", "", "```", *commands, "```", "",
            "`bench.py --probe` first copies 512 MiB device-to-device (one dispatch of the "
            "runtime's `__amd_rocclr_copyBuffer`), which must read and write exactly 524288 "
            "KiB: its readings give each counter's scale.", "",
@@ -169,7 +172,7 @@ def traffic_summary(fetch_csv, write_csv, dram_csv, side, commands):
            f"{np.mean(f_sweep):.1f} | {np.mean(w_sweep):.1f} |",
            f"| sweep kernel, scaled, MB per launch | {fetch_b / 1e6:.1f} | {write_b / 1e6:.1f} |",
            "", f"Scaled traffic per launch: {(fetch_b + write_b) / 1e6:.1f} MB, against "
-           f"{alg / 1e6:.1f} MB of algorithmic bytes (44 B per site).", ""]
+           f"{alg / 1e6:.1f} MB of algorithmic bytes (21.6 B per site).", ""]
     fig = {"kernel": SWEEP_KERNEL, "side": side, "bytes_per_launch": fetch_b + write_b,
            "fetch_bytes": fetch_b, "write_bytes": write_b, "fetch_scale": f_scale,
            "write_scale": w_scale, "kernel_sources_sha256": kernel_sources_sha256()}
@@ -201,7 +204,7 @@ def _fused_variant(name):
     intercept, else None."""
     n = name.replace("gmrf::", "").replace(" ", "")
     for real, tag in (("float", "fp32"), ("double", "fp64")):
-        if f"csr_fused_kernel<{real},false>" in n:
+        if f"csr_fused_kernel<{real},false,false>" in n:
             return tag
     return None
 
@@ -232,7 +235,7 @@ def graph_traffic_summary(fetch_csv, write_csv, commands):
     n = GRAPH_PROBE_SITES
     out = ["# HBM traffic counters: chunked general-graph sweep kernel, Delaunay graph of "
            "1,000,000 sites", "",
-           "Commands (from the repository root on the GPU box):", "", "```", *commands, "```", "",
+           "Commands (from the repository root):", "", "```", *commands, "```", "",
            "`bench.py --probe --probe-graph` first copies 512 MiB device-to-device (one dispatch "
            "of the runtime's `__amd_rocclr_copyBuffer`), which must read and write exactly "
            "524288 KiB: its readings give each counter's scale.", "",
@@ -266,7 +269,7 @@ def _sweep_variant(name):
     n = name.replace("gmrf::", "").replace(" ", "")
     for real, tag in (("float", "fp32"), ("double", "fp64")):
         for v2, ver in (("false", "v1"), ("true", "v2")):
-            if f"lattice_sweep_kernel<{real},LatCfg<8,64,64,512,4>,false,{v2}>" in n:
+            if f"lattice_sweep_kernel<{real},LatCfg<8,64,64,512>,false,{v2}>" in n:
                 return f"{tag} {ver}"
     return None
 
@@ -284,7 +287,7 @@ def counter_summary(csvs, commands):
                     float(r["Counter_Value"]))
     kinds = sorted(vals)
     out = [f"# Counters: lattice sweep kernels, {ROWS}x{COLS}, 8 neighbours", "",
-           "Commands (from the repository root on the GPU box):", "", "```", *commands, "```", "",
+           "Commands (from the repository root):", "", "```", *commands, "```", "",
            "Mean over each kernel's launches in the probe (" +
            ", ".join(f"{k}: {len(next(iter(vals[k].values())))}" for k in kinds) +
            "), per wave (SQ_WAVES per launch in the last row):", "",
@@ -651,13 +654,14 @@ def probe(torch, gmrf, inputs, steps, side=ROWS, variants=False, on_graph=False)
             runs += [(gmrf.FP32_ACC64, 2), (gmrf.FP64, 1), (gmrf.FP64, 2)]
     for prec, v in runs:
         chain = gmrf.Chain(graph, wl["y"], precision=prec, seed=1, rng_version=v)
-        chain.sweep(5, hyper=True)
-        for _ in range(steps):
-            chain.sweep(1, hyper=True)
+        # whole groups of sweeps (five FP32, three FP64) that share a pass over
+        # the accumulators, as in the benchmark's calls
+        chain.sweep(15, hyper=True)
+        chain.sweep(steps, hyper=True)
         torch.cuda.synchronize()
         del chain
     print(json.dumps({"probe": "copy 512 MiB + sweeps", "workload": "delaunay1m" if on_graph
-                      else f"lattice {side}x{side}", "sweeps": steps + 5, "chains": len(runs)}),
+                      else f"lattice {side}x{side}", "sweeps": steps + 15, "chains": len(runs)}),
           flush=True)
 
 

@@ -5,28 +5,33 @@
 //
 //   * Lattice graphs (4- and 8-neighbour stencils, parity colorings): ONE
 //     kernel per sweep.  Each workgroup owns a TH x TW tile of the lattice,
-//     stages the tile plus the halo its phases read (k rings, k the number
-//     of colors; for 8 neighbours one ring fewer before the tile) in LDS,
-//     and runs the k color phases in LDS.  Phase j updates the sites of color
-//     j on the tile grown by k-1-j rings, so the values that later phases read
-//     at the tile border are recomputed locally instead of being exchanged:
-//     the random numbers are keyed by (site, sweep), so a recomputed halo site
-//     is bitwise the value its owning tile computes.  The lattice state is
-//     ping-ponged between two buffers (sweep t reads buffer t&1 and writes the
-//     other), so tiles never see a neighbour's new values through memory.
-//   * General graphs (CSR): one kernel per color over a contiguous color slab
-//     of a color-permuted CSR; sites of one color never read each other, so
-//     the slab is updated in place.
+//     whose 2 x 2 quads its threads keep in registers, stages the tile and a
+//     border of a few cells in LDS, and runs the k color phases there.  The
+//     halo sites whose new values the tile needs are recomputed locally
+//     instead of being exchanged: the random numbers are keyed by (site,
+//     sweep), so a recomputed halo site is bitwise the value its owning tile
+//     computes.  Successive sweeps read and write different buffers (the two
+//     state buffers and, within a call, history slots whose fields the
+//     accumulators take in groups of sweeps), so tiles never see a neighbour's
+//     new values through memory.  A lattice of one tile is swept by one block
+//     for up to kUnitBatch sweeps per launch, from site normals that a launch
+//     over the whole chip draws ahead.
+//   * General graphs (CSR): one kernel per sweep over chunks with recomputed
+//     closures where they fit (the same idea), one block that holds the field
+//     in LDS, or one kernel per color over a contiguous color slab of a
+//     color-permuted CSR; sites of one color never read each other, so the
+//     slab is updated in place.  The binomial model's Polya-Gamma sums are
+//     drawn by launches of their own ahead of a sweep.
 //   * Every sweep kernel fuses the reductions q = x'(D - rho W)x (each edge
 //     counted once, by its higher-colored endpoint, after both ends are final)
 //     and sse = ||y - x||^2 in FP64, and the posterior accumulators.  Blocks
 //     leave FP64 partials; the end of a sweep sums them in fixed slot order
 //     and draws tau and lam on the device, so a sweep has no host round trip.
-//     A lattice sweep kernel begins by ending the previous sweep of its call:
-//     every block sums that sweep's partials and draws the same tau and lam
-//     while its tile loads are in flight (one block records them), so a
-//     lattice sweep is ONE launch; a one-block commit kernel ends the last
-//     sweep of each call.  General graphs end every sweep with that kernel.
+//     A lattice or chunked sweep kernel begins by ending the previous sweep of
+//     its call: every block sums that sweep's partials and draws the same tau
+//     and lam (one block records them), so the sweep is ONE launch; a
+//     one-block commit kernel ends the last sweep of each call.  Color passes
+//     and binomial sweeps end in that kernel.
 //     The rate-free parts of the draws (the Marsaglia-Tsang variate at rate
 //     1, the beta0 normal) depend only on the sweep index: a small kernel
 //     draws them up to kUnitBatch sweeps ahead, so no sweep kernel carries
