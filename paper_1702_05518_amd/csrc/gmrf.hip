@@ -3663,14 +3663,17 @@ private:
 // or current device other than the chain's.
 bool read_report(gmrf_chain *c, DevState *out, char *x, size_t nbytes, hipStream_t s, int *rc)
 {
-    int dev = -1;
-    if (c->device < 0 || sizeof(DevState) + nbytes > kReportBytes ||
-        hipGetDevice(&dev) != hipSuccess || dev != c->device)
+    if (c->device < 0 || sizeof(DevState) + nbytes > kReportBytes)
         return false;
-    if (s && (hipStreamGetDevice(s, &dev) != hipSuccess || dev != c->device))
-        return false;
+    int dev = -1, sdev = c->device;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (s && (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone))
+    if (hipGetDevice(&dev) != hipSuccess ||
+        (s && (hipStreamGetDevice(s, &sdev) != hipSuccess ||
+               hipStreamIsCapturing(s, &cap) != hipSuccess))) {
+        (void)hipGetLastError();            // not the general path's
+        return false;
+    }
+    if (dev != c->device || sdev != c->device || cap != hipStreamCaptureStatusNone)
         return false;
     ReportSlot slot;
     if (!slot.data())
