@@ -434,6 +434,14 @@ __device__ __forceinline__ bool pg_left_keep(double z, double x, double u)
     return u <= exp(w);
 }
 
+// pg_left_keep where only u in (lo, hi) is known: 1 kept, 0 not, -1 undecided.
+__device__ __forceinline__ int pg_left_keep_between(double z, double x, double lo, double hi)
+{
+    const double w = -0.5 * z * z * x;
+    const double ef = (double)__builtin_amdgcn_exp2f((float)w * kLog2ef);
+    return hi <= ef * (1.0 - 1e-4) ? 1 : lo >= ef * (1.0 + 1e-4) ? 0 : -1;
+}
+
 // The first test of the series, Y = u a0 <= a0 - a1, is u <= 1 - 3 E^8 (a1 /
 // a0 = 3 E^8 for both forms of the terms), with 3 E^8 below 0.006 here.  From
 // the single-precision exponential (error below 1e-8 absolute at these
