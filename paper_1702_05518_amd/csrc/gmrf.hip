@@ -4910,7 +4910,7 @@ int gmrf_set_state(gmrf_chain *c, const double *x, double tau, double lam, uint6
         rc = upload_real(c, current_x(c, sweep), x, stream);
         if (rc != GMRF_OK)
             return rc;
-    } else if (is_lattice(c->g) && ((st.sweep ^ sweep) & 1u)) {
+    } else if (current_x(c, sweep) != current_x(c, st.sweep)) {
         // keep x: move it to the buffer the new sweep parity reads
         const size_t bytes = real_size(c->prec) * (size_t)c->g->h.n;
         GMRF_HIP(hipMemcpyAsync(current_x(c, sweep), current_x(c, st.sweep), bytes,
