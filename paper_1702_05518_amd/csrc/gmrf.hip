@@ -1285,8 +1285,13 @@ __device__ __forceinline__ Red lattice_phases(Real *xs, QuadRegs<Real, Cfg> &t, 
         ahead(std::integral_constant<int, 3>{});
         lattice_phase<Real, Cfg, 3, INTERIOR, B0, HALO>(xs, t, at, sc, rd);
     }
+    // The intrinsic prior (rho = 1) has no diagonal term: fields beyond 1e154,
+    // whose squares overflow, still have the q of their edges.
+    double dsq = rd.dsq;
+    if (__builtin_amdgcn_readfirstlane(sc.one_minus_rho == 0.0))
+        dsq = 0.0;
     Red r;
-    r.q = sc.one_minus_rho * (INTERIOR ? (double)Cfg::ST * rd.dsq : rd.dsq) + sc.rho * rd.edge;
+    r.q = sc.one_minus_rho * (INTERIOR ? (double)Cfg::ST * dsq : dsq) + sc.rho * rd.edge;
     r.sse = rd.sse;
     r.rsum = rd.rsum;
     return r;
