@@ -229,8 +229,10 @@ int gmrf_chain_destroy(gmrf_chain *c);
 /* Device workspace bytes of one binomial chain on a general graph g with the
  * given trials (host, n values m_i, original order): the Gaussian layout plus
  * the trials, the Polya-Gamma term chunk tables and sums (about 6 bytes per
- * trial), and a per-site envelope and psi (about 40 bytes per site).
- * Returns 0 and sets the error message on bad input. */
+ * trial for fewer than 2^20 trials in all, 1.5 from there on), and a per-site
+ * envelope and psi (about 40 bytes per site).  Returns 0 and sets the error
+ * message on bad input, and for more trials than a chain takes: the sum of
+ * m_i / 4 (each rounded up) must stay below 2^31 - 256. */
 size_t gmrf_binomial_footprint(const gmrf_graph *g, gmrf_precision p, const int32_t *trials);
 
 /* Create a binomial logit chain (Sec. 3.2) on a general graph: successes
@@ -240,7 +242,7 @@ size_t gmrf_binomial_footprint(const gmrf_graph *g, gmrf_precision p, const int3
  * m->beta0_var >= 0.  a_lam / b_lam / lam0 are not used by the sampler (lam
  * stays lam0).  Batches do not take binomial chains.  The workspace needs
  * gmrf_binomial_footprint(g, p, trials) bytes.  Synchronises.  Errors as gmrf_chain_create,
- * plus GMRF_E_INVALID_ARG for a lattice graph or invalid counts. */
+ * plus GMRF_E_INVALID_ARG for a lattice graph, invalid counts or too many trials. */
 int gmrf_chain_create_binomial(const gmrf_graph *g, const gmrf_model *m, const double *successes,
                                const int32_t *trials, const double *x0, gmrf_precision p,
                                uint64_t seed, uint32_t instance, void *d_ws, size_t ws_bytes,

@@ -4448,18 +4448,25 @@ size_t gmrf_chain_footprint(const gmrf_graph *g, gmrf_precision p)
 constexpr int64_t kMaxChunks = INT32_MAX - kThreads;
 
 // Number of PG term chunks of a binomial chain (trials in original order) and
-// the terms of one; what doesn't fit with short chunks is refused.
+// the terms of one, or -1 for too many trials.  The trials that a chain takes
+// don't depend on its chunks: at most kMaxChunks chunks of kPgLimit terms.
+// Chunks of kPgMany are fewer, and with fewer than kPgManyTerms terms chunks
+// of any length fit.
+constexpr int kPgLimit = 4;
+static_assert(kPgMany >= kPgLimit && kPgManyTerms <= kMaxChunks, "every accepted total fits");
+
 static int64_t count_chunks(const gmrf_graph *g, const int32_t *trials, int *terms)
 {
-    int64_t few = 0, many = 0, total = 0;
+    int64_t few = 0, many = 0, limit = 0, total = 0;
     for (int64_t i = 0; i < g->h.n; ++i) {
-        const int m = std::max(trials[i], 0);
+        const int64_t m = std::max(trials[i], 0);
         total += m;
-        few += ((int64_t)m + kPgFew - 1) / kPgFew;
-        many += ((int64_t)m + kPgMany - 1) / kPgMany;
+        few += (m + kPgFew - 1) / kPgFew;
+        many += (m + kPgMany - 1) / kPgMany;
+        limit += (m + kPgLimit - 1) / kPgLimit;
     }
-    *terms = total >= kPgManyTerms && few <= kMaxChunks ? kPgMany : kPgFew;
-    return *terms == kPgMany ? many : few;
+    *terms = total >= kPgManyTerms ? kPgMany : kPgFew;
+    return limit > kMaxChunks ? -1 : *terms == kPgMany ? many : few;
 }
 
 size_t gmrf_binomial_footprint(const gmrf_graph *g, gmrf_precision p, const int32_t *trials)
@@ -4471,7 +4478,7 @@ size_t gmrf_binomial_footprint(const gmrf_graph *g, gmrf_precision p, const int3
     }
     int terms;
     const int64_t nc = count_chunks(g, trials, &terms);
-    if (nc > kMaxChunks) {
+    if (nc < 0) {
         set_error("binomial_footprint: too many trials in total");
         return 0;
     }
@@ -4554,7 +4561,7 @@ static int chain_create_impl(const char *who, const gmrf_graph *g, const gmrf_mo
     }
     int terms = kPgFew;
     const int64_t n_chunks = binomial ? count_chunks(g, trials, &terms) : 0;
-    if (n_chunks > kMaxChunks)
+    if (n_chunks < 0)
         return fail(GMRF_E_INVALID_ARG, w + ": too many trials in total");
     const size_t need = chain_layout(g, p, nullptr, nullptr, binomial, n_chunks);
     if (!d_ws || ws_bytes < need || (reinterpret_cast<uintptr_t>(d_ws) % kAlign) != 0)
