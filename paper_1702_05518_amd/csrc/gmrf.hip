@@ -3676,8 +3676,8 @@ private:
 
 // Reads the state block and, with x, the current field in layout order
 // (nbytes of it) through a slot.  True when it did (*rc the result); false
-// when the general path has to: no free slot, a field too large, or a stream
-// or current device other than the chain's.
+// when the general path has to: no free slot, a field too large, a stream or
+// current device other than the chain's, or a launch that failed.
 bool read_report(gmrf_chain *c, DevState *out, char *x, size_t nbytes, hipStream_t s, int *rc)
 {
     if (c->device < 0 || sizeof(DevState) + nbytes > kReportBytes)
@@ -3695,15 +3695,18 @@ bool read_report(gmrf_chain *c, DevState *out, char *x, size_t nbytes, hipStream
     ReportSlot slot;
     if (!slot.data())
         return false;
-    const long long words = x ? (long long)(nbytes / 4) : 0;
+    const DevState *st = c->d_state;
+    auto *x0 = static_cast<const uint32_t *>(current_x(c, 0));
+    auto *x1 = static_cast<const uint32_t *>(current_x(c, 1));
+    long long words = x ? (long long)(nbytes / 4) : 0;
+    auto *to = reinterpret_cast<uint32_t *>(slot.data());
     const int blocks = (int)std::min<long long>(std::max<long long>(words / 1024, 1), 32);
-    hipLaunchKernelGGL(report_kernel, dim3(blocks), dim3(kThreads), 0, s, c->d_state,
-                       static_cast<const uint32_t *>(current_x(c, 0)),
-                       static_cast<const uint32_t *>(current_x(c, 1)), words,
-                       reinterpret_cast<uint32_t *>(slot.data()));
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess)
-        e = hipStreamSynchronize(s);
+    // the launch's own status: the thread's last error may be the caller's
+    void *args[] = {&st, &x0, &x1, &words, &to};
+    if (hipLaunchKernel(reinterpret_cast<const void *>(report_kernel), dim3(blocks),
+                        dim3(kThreads), args, 0, s) != hipSuccess)
+        return false;                       // nothing runs: the slot is free again
+    const hipError_t e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         slot.keep();
         *rc = fail(GMRF_E_DEVICE, std::string("state read: ") + hipGetErrorString(e));
