@@ -387,19 +387,18 @@ int gmrf_set_trace(gmrf_chain *c, double *d_trace, int64_t capacity, hipStream_t
  * bytes, at most 32 colors) runs the color passes and the draws in one
  * 512-thread block with the field in LDS -- all the sweeps of a call in one
  * launch, or, for the binomial model, one sweep per launch after the
- * Polya-Gamma launches.  A new binomial chain on a graph with chunk tables
- * (as for shape 1, with 8 bytes more per site of R) runs its color passes as
- * one chunked launch until gmrf_chain_set_tile sets shape 0 or 2 (its results
- * agree with theirs to rounding).  Shape 2 gives bitwise the results of shape 0;
- * shape 1 computes each site's draw the same way but groups the FP64
- * reductions by chunk, so its chains agree with the others to rounding.  A
- * new
- * general-graph chain starts with shape 1 if it fits, else shape 2 if it
- * fits and no color has more than 1024 sites, else shape 0.
+ * Polya-Gamma launches.  The binomial model's shape 1 (a graph with chunk
+ * tables as above, 8 bytes more per site of R, and some trials) runs the
+ * color passes of a sweep as one chunked launch after the Polya-Gamma
+ * launches, the field staying in one buffer.  Shape 2 gives bitwise the
+ * results of shape 0; shape 1 computes each site's draw the same way but
+ * groups the FP64 reductions by chunk, so its chains agree with the others to
+ * rounding.  A new general-graph chain starts with shape 1 if it fits, else
+ * shape 2 if it fits and no color has more than 1024 sites, else shape 0.
  * gmrf_chain_get_tile reports the shape, the tile size (0 x 0 for a general
  * graph) and the threads per block; any output pointer may be NULL.
- * gmrf_chain_set_tile drops the chain's captured sweeps and, when the chain
- * moves to or from shape 1 with the field in the other buffer, copies the
+ * gmrf_chain_set_tile drops the chain's captured sweeps and, when a Gaussian
+ * chain moves to or from shape 1 with the field in the other buffer, copies the
  * field over (synchronising the device); a batch keeps the shapes its chains
  * had when it was created (shape 2 is batched as shape 0).
  * For a shape-2 chain gmrf_sweep_timed reports the duration of the single

@@ -2946,7 +2946,8 @@ struct gmrf_chain {
     int slot_stride = 0;              // partial slots reserved per buffer (lattice: two)
     int total_slots = 0;              // partial slots of one sweep (current tile shape)
     int lat_tile = 0;                 // shape: lattice tile (index into kTiles); general
-                                      // graph: 0 color passes, kPersistent one block
+                                      // graph: 0 color passes, kFused chunks (Gaussian),
+                                      // kPersistent one block
     bool binomial = false;            // binomial logit likelihood (general graphs only)
     int *d_trials = nullptr;          // binomial: m_i in slab order
     int *d_chunk_off = nullptr;       // binomial: PG term chunk tables (see pg_chunk_kernel)
@@ -2956,7 +2957,8 @@ struct gmrf_chain {
     double *d_psi = nullptr;
     int n_chunks = 0;                 // binomial: PG term chunks of all sites
     int chunk_terms = kPgFew;         // and the terms of one chunk
-    bool bin_chunked = false;         // binomial: the color passes as one chunked launch
+    bool bin_chunked = false;         // binomial, shape 1: the color passes as one chunked
+                                      // launch (lat_tile is then not used)
     std::vector<int> pass_blocks;     // CSR: blocks per color pass
     uint64_t host_sweeps = 0;         // sweeps enqueued (host view)
     hipStream_t capture_stream = nullptr;
@@ -3363,11 +3365,11 @@ bool csr_fused_fits(const HostGraph &h, gmrf_precision p, bool binomial)
            (p == GMRF_FP64 ? h.max_lds8 : h.max_lds4) <= kFusedLaunchLds;
 }
 
-// Can a binomial chain's color passes run as one chunked launch?  When the
-// chunks and their psi fit, and the envelope kernel runs (it copies the field
-// that the launch reads).  A new chain then does, until a shape is set: FP64
-// sweeps, chunked / one block / color passes, of 500 sites 29.6 / 34.0 / 40.8
-// us, 2,000 34.0 / 43.0 / 50.2, 4,000 38.1 / 57.3 / 56.7, 14,926 (8 times the
+// Can a binomial chain's color passes run as one chunked launch (shape 1)?
+// When the chunks and their psi fit, and the envelope kernel runs (it copies
+// the field that the launch reads).  A new chain then does: FP64 sweeps,
+// chunked / one block / color passes, of 500 sites 29.6 / 34.0 / 40.8 us,
+// 2,000 34.0 / 43.0 / 50.2, 4,000 38.1 / 57.3 / 56.7, 14,926 (8 times the
 // trials) 90 / - / 114.
 bool binomial_chunks_fit(const HostGraph &h, gmrf_precision p, int64_t n_chunks)
 {
@@ -3410,6 +3412,9 @@ int csr_slots(const gmrf_chain *c, int k)
 // Do all the sweeps of a call run in one launch?  (Shape 2, except for the
 // binomial model, whose Polya-Gamma launches come between sweeps.)
 bool is_persistent(const gmrf_chain *c) { return c->lat_tile == kPersistent && !c->binomial; }
+
+// The shape that gmrf_chain_get_tile reports.
+int shape_of(const gmrf_chain *c) { return c->bin_chunked ? kFused : c->lat_tile; }
 
 // Does the chain draw the hyperparameters inside its sweep kernel (no commit
 // kernel)?
@@ -5029,10 +5034,10 @@ int gmrf_chain_get_tile(const gmrf_chain *c, int32_t *tile, int32_t *tile_rows, 
     if (!c)
         return fail(GMRF_E_INVALID_ARG, "chain_get_tile: NULL chain");
     if (!is_lattice(c->g)) {
-        if (tile) *tile = c->lat_tile;
+        if (tile) *tile = shape_of(c);
         if (tile_rows) *tile_rows = 0;
         if (tile_cols) *tile_cols = 0;
-        if (threads) *threads = c->lat_tile == kPersistent ? kCsrPersistThreads : kThreads;
+        if (threads) *threads = shape_of(c) == kPersistent ? kCsrPersistThreads : kThreads;
         return GMRF_OK;
     }
     const TileShape &t = kTiles[c->lat_tile];
@@ -5050,24 +5055,30 @@ int gmrf_chain_set_tile(gmrf_chain *c, int32_t tile)
         return fail(GMRF_E_INVALID_ARG, "chain_set_tile: NULL chain, or tile not in 0 .. "
                                         "GMRF_NUM_TILES - 1");
     if (!is_lattice(c->g)) {
-        if ((tile == kFused && !csr_fused_fits(c->g->h, c->prec, c->binomial)) ||
-            (tile == kPersistent && !csr_persist_fits(c->g->h, c->prec)))
+        const HostGraph &h = c->g->h;
+        if ((tile == kFused && !(c->binomial ? binomial_chunks_fit(h, c->prec, c->n_chunks)
+                                             : csr_fused_fits(h, c->prec, false))) ||
+            (tile == kPersistent && !csr_persist_fits(h, c->prec)))
             return fail(GMRF_E_INVALID_ARG, "chain_set_tile: a general graph takes shape 0; "
-                                            "shape 1 when its chunks fit (not for the binomial "
-                                            "model); shape 2 when its field fits in LDS (at most "
-                                            "122880 bytes of state) and it has at most 32 colors");
-        if (tile != c->lat_tile || c->bin_chunked) {
-            // shape 1 keeps x in buffer (sweep & 1), the others in buffer 0:
-            // move it when the chain has run an odd number of sweeps
-            if ((tile == kFused) != (c->lat_tile == kFused) && (c->host_sweeps & 1u)) {
-                const size_t bytes = real_size(c->prec) * (size_t)c->g->h.n;
+                                            "shape 1 when its chunks fit (for the binomial model "
+                                            "with their psi, and with some trials); shape 2 when "
+                                            "its field fits in LDS (at most 122880 bytes of "
+                                            "state) and it has at most 32 colors");
+        if (tile != shape_of(c)) {
+            // a Gaussian chain's shape 1 keeps x in buffer (sweep & 1), the
+            // others, and every binomial shape, in buffer 0: move it when the
+            // chain has run an odd number of sweeps
+            if (!c->binomial && (tile == kFused) != (c->lat_tile == kFused) &&
+                (c->host_sweeps & 1u)) {
+                const size_t bytes = real_size(c->prec) * (size_t)h.n;
                 GMRF_HIP(hipDeviceSynchronize());
                 GMRF_HIP(tile == kFused
                              ? hipMemcpy(c->d_x[1], c->d_x[0], bytes, hipMemcpyDeviceToDevice)
                              : hipMemcpy(c->d_x[0], c->d_x[1], bytes, hipMemcpyDeviceToDevice));
             }
-            c->lat_tile = tile;
-            c->bin_chunked = false;
+            c->bin_chunked = c->binomial && tile == kFused;
+            if (!c->bin_chunked)
+                c->lat_tile = tile;
             c->total_slots = csr_slots(c, tile);
             drop_graphs(c);
         }
