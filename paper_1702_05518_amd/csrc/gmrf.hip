@@ -1287,11 +1287,10 @@ __device__ __forceinline__ Red lattice_phases(Real *xs, QuadRegs<Real, Cfg> &t, 
     }
     // The intrinsic prior (rho = 1) has no diagonal term: fields beyond 1e154,
     // whose squares overflow, still have the q of their edges.
-    double dsq = rd.dsq;
-    if (__builtin_amdgcn_readfirstlane(sc.one_minus_rho == 0.0))
-        dsq = 0.0;
     Red r;
-    r.q = sc.one_minus_rho * (INTERIOR ? (double)Cfg::ST * dsq : dsq) + sc.rho * rd.edge;
+    r.q = sc.rho * rd.edge;
+    if (__builtin_amdgcn_readfirstlane(sc.one_minus_rho != 0.0))
+        r.q = fma(sc.one_minus_rho, INTERIOR ? (double)Cfg::ST * rd.dsq : rd.dsq, r.q);
     r.sse = rd.sse;
     r.rsum = rd.rsum;
     return r;
