@@ -260,7 +260,8 @@ int gmrf_chain_create_binomial(const gmrf_graph *g, const gmrf_model *m, const d
  * every block); a one-block commit kernel ends the call's last sweep.  A
  * general graph in shape 0 runs one kernel per color and the commit kernel
  * after every sweep; shape 2 runs the whole call in one launch (a lattice:
- * 128 sweeps per launch, after one that draws their site normals).  With
+ * at most 128 sweeps per launch, after one that draws their site normals; see
+ * gmrf_chain_set_ahead).  With
  * GMRF_WITH_HYPER a small kernel
  * draws the rate-free parts of the hyperparameter draws (which depend only
  * on the sweep index) before every 128 sweeps.  Sec. 2.3, Algorithm 1; the
@@ -370,8 +371,8 @@ int gmrf_set_trace(gmrf_chain *c, double *d_trace, int64_t capacity, hipStream_t
  * lattice sweep run tile by tile): shape 0 is a 64 x 64 tile with 512
  * threads, shape 1 a 32 x 32 tile with 256 threads; shape 2 (lattices of at
  * most 64 x 64 sites) is shape 0's single tile swept by a persistent
- * one-block kernel that runs 128 sweeps of a gmrf_sweep call, with their
- * draws, per launch (bitwise the results of shape 0).  A new lattice chain
+ * one-block kernel that runs up to 128 sweeps of a gmrf_sweep call, with
+ * their draws, per launch (bitwise the results of shape 0).  A new lattice chain
  * starts with shape 2 if the lattice fits one 64 x 64 tile, else with shape 0
  * if that gives at least 512 tiles, else shape 1.  Shapes 0 and 1 group the
  * FP64 reductions differently (results agree to rounding, not bit for bit);
@@ -408,6 +409,19 @@ int gmrf_set_trace(gmrf_chain *c, double *d_trace, int64_t capacity, hipStream_t
 int gmrf_chain_get_tile(const gmrf_chain *c, int32_t *tile, int32_t *tile_rows, int32_t *tile_cols,
                         int32_t *threads);
 int gmrf_chain_set_tile(gmrf_chain *c, int32_t tile);
+
+/* Site normals drawn ahead: a shape-2 lattice chain draws the site normals of
+ * as many sweeps as its memory for them holds in one launch, then runs those
+ * sweeps in the next.  The workspace holds those of 2 sweeps (FP64) or 4
+ * (FP32) beside what else it is for.  gmrf_chain_ahead_bytes: bytes for the
+ * 128 sweeps that a launch runs at most (about 512 per site FP32, 1024 FP64);
+ * 0 for a graph whose chains have no shape-2 lattice kernel.
+ * gmrf_chain_set_ahead lends a chain a device buffer of that or fewer bytes
+ * (256-byte aligned, kept alive until the chain is destroyed or lent another;
+ * NULL and 0: none), and drops the chain's captured sweeps.  Results are the
+ * same bits with any buffer; batches do not use it.  Host-only calls. */
+size_t gmrf_chain_ahead_bytes(const gmrf_graph *g, gmrf_precision p);
+int gmrf_chain_set_ahead(gmrf_chain *c, void *d_ahead, size_t bytes);
 
 /* Autotune the launch shape of a chain (a lattice, or a Gaussian chain on a
  * general graph; not binomial chains): time `reps` (1 .. 100000) whole

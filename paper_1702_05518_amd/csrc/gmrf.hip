@@ -1590,44 +1590,53 @@ __global__ __launch_bounds__(Cfg::NT, (kLatWaves<Real, Cfg>)) void lattice_sweep
 // One block is bound by the length of its chain, and the site normals, which
 // depend only on (site, sweep), were most of it: the ahead kernel draws those
 // of all the launch's sweeps over the whole chip (and the rate-free parts of
-// the end-of-sweep draws), into z in the order this kernel's threads read
-// them: quad i of thread tid in sweep s is the four values from
-// 4 ((s NQ + i) NT + tid).  Per sweep, drawn in place -> ahead: 50 x 50 FP64
-// with intercept 8.2 -> 3.9 us, 64 x 64 4-neighbour FP64 7.3 -> 3.1 us, 64 x 64
-// FP32 5.8 -> 3.4 us.  What is left is the k phases' LDS round trips and the
-// FP64 chain of the end of the sweep.
-template <typename Real, typename Cfg, bool V2>
-__global__ __launch_bounds__(Cfg::NT) void lattice_ahead_kernel(Real *z, SweepArgs a, int rows,
-                                                                int cols, int cnt)
+// the end-of-sweep draws), into z by the lattice's own quads (ahead_quads, in
+// row order): quad q of sweep s is the four values from 4 (s quads + q).  Per
+// sweep, drawn in place -> ahead: 50 x 50 FP64 with intercept 8.2 -> 3.9 us,
+// 64 x 64 4-neighbour FP64 7.3 -> 3.1 us, 64 x 64 FP32 5.8 -> 3.4 us.  What is
+// left is the k phases' LDS round trips and the FP64 chain of the end of the
+// sweep.
+__host__ __device__ constexpr int ahead_quads(int rows, int cols)
 {
-    if ((int)blockIdx.x == cnt * Cfg::NQ) {
-        unit_ring_fill(a, 0, cnt);
+    return ((rows + 1) / 2) * ((cols + 1) / 2);
+}
+
+// Row y of the grid: sweep y's quads; row cnt: the rate-free draws.
+template <typename Real, bool V2>
+__global__ __launch_bounds__(kThreads) void lattice_ahead_kernel(Real *z, SweepArgs a, int rows,
+                                                                 int cols, int cnt)
+{
+    const int s = (int)blockIdx.y;
+    if (s == cnt) {
+        if (blockIdx.x == 0)
+            unit_ring_fill(a, 0, cnt);
         return;
     }
-    const int s = (int)blockIdx.x / Cfg::NQ, i = (int)blockIdx.x % Cfg::NQ;
-    const int tid = (int)threadIdx.x;
-    const unsigned t = (unsigned)a.st->sweep + (unsigned)s;
-    const int r = quad_row<Cfg>(tid, i), c = quad_col<Cfg>(tid);
-    if (r >= rows || c >= cols)
+    const int quads = ahead_quads(rows, cols), qc = (cols + 1) / 2;
+    const int q = (int)blockIdx.x * kThreads + (int)threadIdx.x;
+    if (q >= quads)
         return;
+    const unsigned t = (unsigned)a.st->sweep + (unsigned)s;
+    const int r = 2 * (q / qc), c = 2 * (q - q / qc * qc);
     Real v[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k)     // sites outside the lattice draw too; no one reads them
         v[k] = lattice_normal<Real, V2>(a, t, r + (k >> 1), c + (k & 1), cols);
     using L = typename Pair<Real>::Lds;
-    L *const out = reinterpret_cast<L *>(z + 4 * ((size_t)blockIdx.x * Cfg::NT + tid));
+    L *const out = reinterpret_cast<L *>(z + 4 * ((size_t)s * quads + q));
     out[0] = L{v[0], v[1]};
     out[1] = L{v[2], v[3]};
 }
 
+// The normals of the thread's quads (quad[i]: their byte offsets in a sweep's).
 template <typename Real, typename Cfg>
-__device__ __forceinline__ void load_ahead(Real (&v)[Cfg::NQ][4], const Real *z, int s)
+__device__ __forceinline__ void load_ahead(Real (&v)[Cfg::NQ][4], const Real *z,
+                                           const unsigned (&quad)[Cfg::NQ])
 {
     using L = typename Pair<Real>::Lds;
 #pragma unroll
     for (int i = 0; i < Cfg::NQ; ++i) {
-        const L *const p = reinterpret_cast<const L *>(
-            z + 4 * ((size_t)(s * Cfg::NQ + i) * Cfg::NT + threadIdx.x));
+        const L *const p = reinterpret_cast<const L *>(at_bytes(z, quad[i]));
         const L a = p[0], b = p[1];
         v[i][0] = a.x;
         v[i][1] = a.y;
@@ -1657,8 +1666,16 @@ __global__ __launch_bounds__(Cfg::NT) void lattice_persistent_kernel(LatArgs<Rea
     load_quads<Real, Cfg, false>(q.y, la.y, at);
     load_quads<double, Cfg, false>(s1r, a.s1, at);
     load_quads<double, Cfg, false>(s2r, a.s2, at);
+    const int quads = ahead_quads(la.rows, la.cols);
+    unsigned quad[NQ];  // a thread without a quad in the lattice reads the first one's
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+        const int r = quad_row<Cfg>((int)threadIdx.x, i), c = quad_col<Cfg>((int)threadIdx.x);
+        const int q = r < la.rows && c < la.cols ? r / 2 * ((la.cols + 1) / 2) + c / 2 : 0;
+        quad[i] = 4u * (unsigned)sizeof(Real) * (unsigned)q;
+    }
     Real znext[NQ][4];
-    load_ahead<Real, Cfg>(znext, z, 0);
+    load_ahead<Real, Cfg>(znext, z, quad);
     // the ring lies outside the lattice: 0
     for (int i = (int)threadIdx.x; i < Cfg::LH * Cfg::LW; i += NT)
         xs[i] = (Real)0;
@@ -1692,7 +1709,7 @@ __global__ __launch_bounds__(Cfg::NT) void lattice_persistent_kernel(LatArgs<Rea
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 q.z[i][k] = znext[i][k];
-        load_ahead<Real, Cfg>(znext, z, min(s + 1, nsweeps - 1));
+        load_ahead<Real, Cfg>(znext, z + (size_t)min(s + 1, nsweeps - 1) * (4 * quads), quad);
         const UnitDraws u = a.with_hyper && threadIdx.x < 2 ? a.units[2 * s + lane]
                                                             : UnitDraws{0.0, 0.0, false};
         Red rd = lattice_phases<Real, Cfg, false, B0, false>(xs, q, at, sc, [](auto) {});
@@ -2941,7 +2958,8 @@ struct gmrf_chain {
     double *d_partials = nullptr;
     double *d_stats = nullptr;
     UnitDraws *d_units = nullptr;     // ring of unit variates drawn ahead of the sweeps
-    void *d_ahead = nullptr;          // one-tile lattices: normals of kUnitBatch sweeps
+    void *d_ahead = nullptr;          // one-tile lattices: site normals drawn ahead (the
+    int ahead_sweeps = 0;             // statistics area or the caller's), and of how many sweeps
     int slot_stride = 0;              // partial slots reserved per buffer (lattice: two)
     int total_slots = 0;              // partial slots of one sweep (current tile shape)
     int lat_tile = 0;                 // shape: lattice tile (index into kTiles); general
@@ -3072,6 +3090,23 @@ int max_lattice_blocks(const HostGraph &h)
     return m;
 }
 
+// Bytes of one sweep's site normals drawn ahead (0: a chain on this graph
+// draws none).
+size_t ahead_sweep_bytes(const gmrf_graph *g, gmrf_precision p)
+{
+    return is_lattice(g) && tile_fits(g->h, kPersistent)
+               ? real_size(p) * 4 * (size_t)ahead_quads(g->h.rows, g->h.cols)
+               : 0;
+}
+
+// Draw ahead into bytes of device memory.
+void set_ahead(gmrf_chain *c, void *mem, size_t bytes)
+{
+    const size_t each = ahead_sweep_bytes(c->g, c->prec);
+    c->d_ahead = mem;
+    c->ahead_sweeps = each ? (int)std::min<size_t>(bytes / each, kUnitBatch) : 0;
+}
+
 // Chain workspace layout; ptrs may be NULL to only compute the size.  A
 // binomial chain adds the trials, the term chunk tables, and per-site
 // envelopes and psi.
@@ -3113,9 +3148,6 @@ size_t chain_layout(const gmrf_graph *g, gmrf_precision p, char *base, gmrf_chai
     char *part = take(8 * kPartials * (size_t)std::max(reserve, 1) * 2);
     char *units = take(sizeof(UnitDraws) * 2 * kUnitRows);
     char *stats = take(16 * n);
-    char *ahead = is_lattice(g) && tile_fits(g->h, kPersistent)
-                      ? take(rs * kTiles[0].th * kTiles[0].tw * kUnitBatch)
-                      : nullptr;
     char *trials = binomial ? take(4 * n) : nullptr;
     char *chunk_off = binomial ? take(4 * (size_t)(n + 1)) : nullptr;
     char *chunk_site = binomial ? take(4 * (size_t)std::max<int64_t>(n_chunks, 1)) : nullptr;
@@ -3138,7 +3170,7 @@ size_t chain_layout(const gmrf_graph *g, gmrf_precision p, char *base, gmrf_chai
         c->d_partials = reinterpret_cast<double *>(part);
         c->d_stats = reinterpret_cast<double *>(stats);
         c->d_units = reinterpret_cast<UnitDraws *>(units);
-        c->d_ahead = ahead;
+        set_ahead(c, stats, align_up(16 * (size_t)n));
         c->slot_stride = std::max(reserve, 1);
         c->total_slots = slots;
         c->pass_blocks = pass_blocks;
@@ -3268,8 +3300,20 @@ void launch_lattice(const gmrf_chain *c, const SweepArgs &a, hipStream_t s, hipE
         launch_lattice_shape<Real, ST, 1>(c, a, s, ev0, ev1, rel, fold, plan);
 }
 
-// nsweeps sweeps of a shape-2 lattice chain: per kUnitBatch sweeps, the draws
-// ahead and the persistent kernel.
+// nsweeps sweeps of a shape-2 lattice chain: per ahead_sweeps of them, the
+// draws ahead and the persistent kernel.  The statistics area, which nothing
+// else uses between a call's start and its end here, always holds one sweep
+// (16 n bytes rounded up to kAlign against at most 8 (rows + 1) (cols + 1)).
+//
+// Ahead for calls of any length: whole calls of 1 / 2 / 4 / 16 / 128 sweeps
+// with the host's wait, normals drawn in the block itself / ahead of all of
+// them / ahead into the statistics area: 48 x 40 FP64 25.2 / 30.7 / 41.5 /
+// 105 / 703 us, 25.1 / 28.7 / 35.1 / 74 / 438, 25.5 / 28.8 / 43.4 / 133 / 943;
+// 64 x 64 FP32 23.7 / 28.0 / 36.5 / 88 / 568, 25.6 / 28.1 / 34.9 / 75 / 448,
+// 25.8 / 28.7 / 35.6 / 100 / 694; 16 x 16 FP64 22.5 / 25.7 / 32.3 / 71 / 433,
+// 23.7 / 26.2 / 31.8 / 62 / 340, 23.9 / 26.4 / 39.1 / 115 / 817.  A second
+// kernel that draws for itself would save calls of one sweep at most 2 us, and
+// long calls of chains that were lent no memory a fifth to a half.
 template <typename Real, int ST>
 void launch_persistent_typed(const gmrf_chain *c, const SweepArgs &a, int nsweeps, hipStream_t s,
                              hipEvent_t ev0, hipEvent_t ev1)
@@ -3277,19 +3321,20 @@ void launch_persistent_typed(const gmrf_chain *c, const SweepArgs &a, int nsweep
     const LatArgs<Real> la = lattice_args<Real>(c);
     using Cfg = LatticeCfg<ST, 0>;
     Real *const z = static_cast<Real *>(c->d_ahead);
-    auto ahead = c->model.rng_version == 2 ? lattice_ahead_kernel<Real, Cfg, true>
-                                           : lattice_ahead_kernel<Real, Cfg, false>;
+    auto ahead = c->model.rng_version == 2 ? lattice_ahead_kernel<Real, true>
+                                           : lattice_ahead_kernel<Real, false>;
     auto kern = c->model.intercept ? lattice_persistent_kernel<Real, Cfg, true>
                                    : lattice_persistent_kernel<Real, Cfg, false>;
-    for (int i = 0; i < nsweeps; i += kUnitBatch) {
-        const int cnt = std::min(kUnitBatch, nsweeps - i);
+    const int blocks = (ahead_quads(la.rows, la.cols) + kThreads - 1) / kThreads;
+    for (int i = 0; i < nsweeps; i += c->ahead_sweeps) {
+        const int cnt = std::min(c->ahead_sweeps, nsweeps - i);
         const hipEvent_t e0 = i == 0 ? ev0 : nullptr, e1 = i + cnt == nsweeps ? ev1 : nullptr;
-        const dim3 grid(cnt * Cfg::NQ + 1);
+        const dim3 grid(blocks, cnt + 1);
         if (e0)
-            hipExtLaunchKernelGGL(ahead, grid, dim3(Cfg::NT), 0, s, e0, nullptr, 0, z, a, la.rows,
+            hipExtLaunchKernelGGL(ahead, grid, dim3(kThreads), 0, s, e0, nullptr, 0, z, a, la.rows,
                                   la.cols, cnt);
         else
-            hipLaunchKernelGGL(ahead, grid, dim3(Cfg::NT), 0, s, z, a, la.rows, la.cols, cnt);
+            hipLaunchKernelGGL(ahead, grid, dim3(kThreads), 0, s, z, a, la.rows, la.cols, cnt);
         if (e1)
             hipExtLaunchKernelGGL(kern, dim3(1), dim3(Cfg::NT), 0, s, nullptr, e1, 0, la, a, z,
                                   cnt);
@@ -5044,6 +5089,33 @@ int gmrf_chain_get_tile(const gmrf_chain *c, int32_t *tile, int32_t *tile_rows, 
     if (tile_rows) *tile_rows = t.th;
     if (tile_cols) *tile_cols = t.tw;
     if (threads) *threads = t.nt;
+    return GMRF_OK;
+}
+
+size_t gmrf_chain_ahead_bytes(const gmrf_graph *g, gmrf_precision p)
+{
+    clear_error();
+    if (!g || (p != GMRF_FP64 && p != GMRF_FP32_ACC64)) {
+        set_error("chain_ahead_bytes: NULL graph or bad precision");
+        return 0;
+    }
+    return align_up(kUnitBatch * ahead_sweep_bytes(g, p));
+}
+
+int gmrf_chain_set_ahead(gmrf_chain *c, void *d_ahead, size_t bytes)
+{
+    clear_error();
+    if (!c || (!d_ahead && bytes))
+        return fail(GMRF_E_INVALID_ARG, "chain_set_ahead: NULL chain, or bytes without a buffer");
+    if (reinterpret_cast<uintptr_t>(d_ahead) % kAlign != 0)
+        return fail(GMRF_E_WORKSPACE, "chain_set_ahead: the buffer must be 256-byte aligned");
+    set_ahead(c, c->d_stats, align_up(16 * (size_t)c->g->h.n));
+    const int own = c->ahead_sweeps;
+    if (d_ahead)
+        set_ahead(c, d_ahead, bytes);
+    if (c->ahead_sweeps < own)
+        set_ahead(c, c->d_stats, align_up(16 * (size_t)c->g->h.n));
+    drop_graphs(c);     // captured sweeps carry the old buffer
     return GMRF_OK;
 }
 

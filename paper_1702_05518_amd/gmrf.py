@@ -64,6 +64,8 @@ _SIGS = {
     "gmrf_chain_create": ([C.c_void_p, C.POINTER(Model), C.POINTER(C.c_double),
                            C.POINTER(C.c_double), C.c_int, C.c_uint64, C.c_uint32, C.c_void_p,
                            C.c_size_t, C.c_void_p, C.POINTER(C.c_void_p)], C.c_int),
+    "gmrf_chain_ahead_bytes": ([C.c_void_p, C.c_int], C.c_size_t),
+    "gmrf_chain_set_ahead": ([C.c_void_p, C.c_void_p, C.c_size_t], C.c_int),
     "gmrf_chain_destroy": ([C.c_void_p], C.c_int),
     "gmrf_binomial_footprint": ([C.c_void_p, C.c_int, C.POINTER(C.c_int32)], C.c_size_t),
     "gmrf_chain_create_binomial": ([C.c_void_p, C.POINTER(Model), C.POINTER(C.c_double),
@@ -246,11 +248,14 @@ class Chain:
     def __init__(self, graph: Graph, y, *, precision=FP64, seed=1, instance=0, x0=None,
                  a_tau=1.0, b_tau=1.0, a_lam=1.0, b_lam=1.0, tau0=1.0, lam0=1.0, burn_in=0,
                  intercept=False, beta0=0.0, trials=None, beta0_var=0.0, rng_version=1,
-                 stream=None):
+                 stream=None, ahead=True):
         """With ``trials`` (m_i) the chain is the binomial logit model and y
         holds the successes Y_i; ``beta0_var`` is then the prior variance of
         beta0 (0 = flat).  ``rng_version`` 2 selects the paired site normals
-        (lattices of width a multiple of 4)."""
+        (lattices of width a multiple of 4).  ``ahead``: lattices of at most
+        64 x 64 sites also get memory for the site normals of 128 sweeps drawn
+        ahead (about 1 KB per site FP64, beyond ``footprint``), which a chain
+        that only batches sweep does without."""
         L = lib()
         self.graph = graph
         self.n = graph.n
@@ -270,7 +275,8 @@ class Chain:
         if need == 0:
             raise GmrfError(E_INVALID_ARG, last_error())
         self.footprint = need
-        self.ws = _workspace(need, graph.device)
+        more = L.gmrf_chain_ahead_bytes(graph.handle, precision) if ahead else 0
+        self.ws = _workspace(need + more, graph.device)
         yy = np.ascontiguousarray(y, dtype=np.float64)
         if yy.size != self.n:
             raise ValueError("y must have n entries")
@@ -287,6 +293,8 @@ class Chain:
                                        C.c_void_p(self.ws.data_ptr()), need,
                                        _stream_handle(stream), C.byref(h)))
         self.handle = h
+        if more:
+            _check(L.gmrf_chain_set_ahead(h, C.c_void_p(self.ws.data_ptr() + need), more))
 
     def __del__(self):
         h = getattr(self, "handle", None)

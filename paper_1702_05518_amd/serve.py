@@ -119,7 +119,8 @@ class Server:
                 break
             self.waiting.popleft()
             job.chain = gmrf.Chain(job.graph, job.y, precision=job.precision, seed=job.seed,
-                                   instance=job.instance, stream=self._create_stream())
+                                   instance=job.instance, stream=self._create_stream(),
+                                   ahead=False)
             job.t_admit = now
             self.used += need
             self.active.append(job)
