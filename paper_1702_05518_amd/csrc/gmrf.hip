@@ -4402,6 +4402,7 @@ int gmrf_graph_create(const gmrf_graph_desc *d, void *d_ws, size_t ws_bytes, hip
         delete g;
         return rc;
     }
+    drop_chunk_rows(&g->h);
     if (!is_lattice(g)) {
         const size_t need = graph_device_bytes(g->h);
         if (!d_ws || ws_bytes < need || (reinterpret_cast<uintptr_t>(d_ws) % kAlign) != 0) {

@@ -530,24 +530,26 @@ void build_chunks(HostGraph *g, const std::vector<int32_t> &cell)
             off = (uint16_t)(off + (g->row_ptr[u + 1] - g->row_ptr[u]));
         }
         g->loc_row.push_back(off);
-        // each chunk's rows and neighbours start on a 16-byte boundary, so the
-        // kernel stages them with 16-byte loads
+        // the rows in groups of four, filled with slot nloc
+        const uint16_t *row = g->loc_row.data() + g->ch_row.back();
+        const uint16_t *adj = g->loc_adj.data() + g->ch_adj.back();
+        const size_t grp0 = g->loc_grp.size() / 4;
+        const uint16_t fill = (uint16_t)(4 * nloc);
+        g->loc_grp.insert(g->loc_grp.end(), 4, fill);
+        for (size_t i = 0; i < R.size(); ++i) {
+            g->loc_head.push_back((uint32_t)(g->loc_grp.size() / 4 - grp0) << 16 |
+                                  (uint32_t)(row[i + 1] - row[i]));
+            for (int32_t e = row[i]; e < row[i + 1]; ++e)
+                g->loc_grp.push_back((uint16_t)(4 * adj[e]));
+            while (g->loc_grp.size() % 4)
+                g->loc_grp.push_back(fill);
+        }
+        // each chunk's part of a table starts on a 16-byte boundary (the sweep
+        // kernel stages heads and groups with 16-byte loads)
         while (g->loc_row.size() % 8)
             g->loc_row.push_back(0);
         while (g->loc_adj.size() % 8)
             g->loc_adj.push_back(0);
-        // the rows in groups of four, filled with slot nloc
-        const size_t grp0 = g->loc_grp.size() / 4;
-        const uint16_t fill = (uint16_t)(4 * nloc);
-        g->loc_grp.insert(g->loc_grp.end(), 4, fill);
-        for (int32_t u : R) {
-            const uint32_t deg = (uint32_t)(g->row_ptr[u + 1] - g->row_ptr[u]);
-            g->loc_head.push_back((uint32_t)(g->loc_grp.size() / 4 - grp0) << 16 | deg);
-            for (int32_t e = g->row_ptr[u]; e < g->row_ptr[u + 1]; ++e)
-                g->loc_grp.push_back((uint16_t)(4 * slot[g->col[e]]));
-            while (g->loc_grp.size() % 4)
-                g->loc_grp.push_back(fill);
-        }
         while (g->loc_head.size() % 4)
             g->loc_head.push_back(0);
         while (g->loc_grp.size() % 8)
@@ -615,6 +617,15 @@ int fail(int status, const std::string &msg)
     return status;
 }
 const char *error_cstr() { return g_error.c_str(); }
+
+void drop_chunk_rows(HostGraph *g)
+{
+    auto free = [](auto &v) { std::decay_t<decltype(v)>().swap(v); };
+    free(g->ch_row);
+    free(g->ch_adj);
+    free(g->loc_row);
+    free(g->loc_adj);
+}
 
 size_t graph_device_bytes(const HostGraph &g)
 {

@@ -43,7 +43,7 @@ struct HostGraph {
     int32_t max_local = 0;               // most staged sites of any chunk
     int32_t max_r = 0;                   // most recomputed (R) sites of any chunk
     int32_t max_adj = 0;                 // most local neighbour entries of any chunk
-    int64_t max_image4 = 0, max_image8 = 0;   // largest chunk LDS image, FP32 / FP64 values
+    int64_t max_image4 = 0, max_image8 = 0;   // largest chunk_lds_bytes, FP32 / FP64 values
     bool chunks_ok = false;              // every chunk within the LDS and index limits
     std::vector<int32_t> ch_loc;         // nchunks + 1: first staged site of each chunk
     std::vector<int32_t> ch_row;         // nchunks + 1: first local row offset of each chunk
@@ -56,10 +56,11 @@ struct HostGraph {
     std::vector<uint16_t> loc_row;       // per chunk, |R_b| + 1 offsets into its local neighbours
     std::vector<uint16_t> loc_adj;       // local slots of the neighbours of each R_b site,
                                          // ascending original id
-    // The same rows as the sweep kernel reads them: cut into groups of four
-    // neighbours, short groups filled with the chunk's slot past its staged
-    // sites, which holds 0.  A neighbour is four times its slot; group 0 of a
-    // chunk is all filling.  Both parts fill whole 16-byte vectors per chunk.
+    // The same rows as the sweep kernel reads them, made from those above:
+    // groups of four neighbours, short groups filled with the chunk's slot past
+    // its staged sites, which holds 0.  A neighbour is four times its slot;
+    // group 0 of a chunk is all filling.  Both parts fill whole 16-byte vectors
+    // per chunk.
     std::vector<int32_t> ch_head;        // nchunks + 1: first row head of each chunk
     std::vector<int32_t> ch_grp;         // nchunks + 1: first group of each chunk
     std::vector<uint32_t> loc_head;      // per R_b site: first group << 16 | degree
@@ -67,15 +68,16 @@ struct HostGraph {
     int64_t max_lds4 = 0, max_lds8 = 0;  // largest LDS image of the kernel, FP32 / FP64 values
 };
 
-// Owned sites per chunk, and the limits of a chunk: its LDS image (staged
-// values, y and normal variates of the R sites, local rows and neighbours)
-// with FP64 and with FP32 values, and 16-bit local offsets.  A block lays out
-// its own chunk's image; a launch reserves the largest image of the graph
-// (at most kFusedLaunchLds).  The FP64 cap keeps four blocks of the chunked
-// sweep kernel (with its static LDS) within a CU's 160 KB; the FP32 cap
-// (six blocks fit from 25,000 B) splits the largest few percent of the
-// chunks further, whose closures set the tail of a sweep (measured on
-// Delaunay graphs: 1M sites 36.9 -> 33.2 us, 15k sites 15.8 -> 14.8 us).
+// Owned sites per chunk, and the limits of a chunk: its size with FP64 and
+// with FP32 values (chunk_lds_bytes), and 16-bit local offsets.  A block lays
+// out its own chunk's LDS image, up to half as large again (sweep_lds_bytes);
+// a launch reserves the largest image of the graph (at most kFusedLaunchLds).
+// On Delaunay graphs of 15k to 1M sites the largest image is 36.5 to 36.7 KB
+// FP64, so four blocks of the sweep kernel (with its static LDS) fit within a
+// CU's 160 KB, and 26.1 to 26.2 KB FP32, so five do.  The FP32 cap splits the
+// largest few percent of the chunks further than the FP64 cap does, whose
+// closures set the tail of a sweep (measured on Delaunay graphs: 1M sites
+// 36.9 -> 33.2 us, 15k sites 15.8 -> 14.8 us).
 constexpr int32_t kChunkSites = 512;
 constexpr int64_t kFusedLdsBytes = 38000;
 constexpr int64_t kFusedLdsBytes32 = 21800;
@@ -86,8 +88,9 @@ constexpr int32_t kFusedMaxColors = 32;  // colorings with more colors sweep by 
 // Bytes of a chunk with real_bytes-byte values (values of the staged sites,
 // then y and the sweep's normal variate of each R site, then the R sites'
 // local row offsets and neighbours, each part 16-byte aligned): the measure
-// that the caps bound.  The kernel's image (sweep_lds_bytes) is larger by
-// what fills the neighbour groups, at most twice it at degree 1.
+// that the caps bound.  The kernel's image (sweep_lds_bytes) is larger by its
+// 32-bit row heads and by what fills the neighbour groups, most at degree 1:
+// 24 against 16 bytes per site FP32, 36 against 28 FP64.
 inline int64_t chunk_lds_bytes(int64_t nloc, int64_t nr, int64_t nadj, int64_t real_bytes)
 {
     auto al = [](int64_t b) { return (b + 15) / 16 * 16; };
@@ -103,7 +106,7 @@ inline int64_t sweep_lds_bytes(int64_t nloc, int64_t nr, int64_t ngrp, int64_t r
     return al(real_bytes * (nloc + 1)) + 2 * al(real_bytes * nr) + al(4 * nr) + al(8 * ngrp);
 }
 
-// Does a chunk's image fit both caps?
+// Is a chunk within both caps?
 inline bool chunk_fits_lds(int64_t nloc, int64_t nr, int64_t nadj)
 {
     return chunk_lds_bytes(nloc, nr, nadj, 8) <= kFusedLdsBytes &&
@@ -116,6 +119,10 @@ int build_host_graph(const gmrf_graph_desc *d, HostGraph *out);
 // First-fit greedy coloring in ascending id order.
 int greedy_coloring_host(int64_t n, const int64_t *row_ptr, const int32_t *col, int32_t *color,
                          int32_t *k);
+
+// Free the rows that loc_head and loc_grp were made from, which nothing reads
+// after that (18 bytes per site of a Delaunay graph).
+void drop_chunk_rows(HostGraph *g);
 
 // Bytes of the device form of a graph (a built host form).
 size_t graph_device_bytes(const HostGraph &g);
