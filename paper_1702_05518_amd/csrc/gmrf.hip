@@ -3012,6 +3012,7 @@ struct gmrf_batch {
     hipStream_t capture_stream = nullptr;
     // batches of lattices and graphs: the graphs' stream within a call
     hipStream_t side = nullptr;
+    int side_device = -1;
     hipEvent_t side_start = nullptr, side_end = nullptr;
     std::map<std::pair<int, unsigned>, hipGraphExec_t> graphs;
     std::vector<hipGraph_t> graph_defs;
@@ -4192,10 +4193,22 @@ void launch_batch_sweep_kernels(const gmrf_batch *b, int hyper, int rel, int fol
 // kSplitSweeps the events cost more than the overlap gives.
 constexpr int kSplitSweeps = 6;
 
+// The device of a stream (NULL: the current one), or -1.
+int stream_device(hipStream_t s)
+{
+    int dev = -1;
+    if ((s ? hipStreamGetDevice(s, &dev) : hipGetDevice(&dev)) == hipSuccess)
+        return dev;
+    (void)hipGetLastError();
+    return -1;
+}
+
+// A wait that cannot be had ends the call's launches; the caller reports it.
 void launch_batch_sweeps(const gmrf_batch *b, int nsweeps, unsigned flags, hipStream_t s)
 {
     const int hyper = (flags & GMRF_WITH_HYPER) ? 1 : 0;
-    const bool split = b->side && nsweeps >= kSplitSweeps;
+    // an event takes no stream of another device
+    const bool split = b->side && nsweeps >= kSplitSweeps && stream_device(s) == b->side_device;
     auto wait = [](hipStream_t waits, hipEvent_t e, hipStream_t runs) {
         return hipEventRecord(e, runs) == hipSuccess &&
                hipStreamWaitEvent(waits, e, 0) == hipSuccess;
@@ -4203,14 +4216,17 @@ void launch_batch_sweeps(const gmrf_batch *b, int nsweeps, unsigned flags, hipSt
     hipStream_t graphs = s;
     for (int i = 0; i < nsweeps; ++i) {
         if (i % kUnitBatch == 0) {
-            if (graphs != s)
-                (void)wait(s, b->side_end, graphs);
+            if (graphs != s && !wait(s, b->side_end, graphs))
+                return;
             if (hyper)
                 hipLaunchKernelGGL(unit_draw_batch_kernel, dim3((unsigned)b->chains.size()),
                                    dim3(kUnitThreads), 0, s, b->unit_args, i,
                                    std::min(kUnitBatch, nsweeps - i));
-            if (split)
-                graphs = wait(b->side, b->side_start, s) ? b->side : s;
+            if (split) {
+                if (!wait(b->side, b->side_start, s))
+                    return;
+                graphs = b->side;
+            }
         }
         if (b->prec == GMRF_FP64)
             launch_batch_sweep_kernels<double>(b, hyper, i, i > 0 ? 1 : 0, nsweeps, s, graphs);
@@ -4220,8 +4236,8 @@ void launch_batch_sweeps(const gmrf_batch *b, int nsweeps, unsigned flags, hipSt
             hipLaunchKernelGGL(commit_batch_kernel, dim3((unsigned)b->n_csr),
                                dim3(kFinishThreads), 0, graphs, b->csr_commit, 0, 1, hyper);
     }
-    if (graphs != s)
-        (void)wait(s, b->side_end, graphs);
+    if (graphs != s && !wait(s, b->side_end, graphs))
+        return;
     if (b->n_lat > 0 && nsweeps > 0)   // one-launch chains: the call's last sweep
         hipLaunchKernelGGL(commit_batch_kernel, dim3((unsigned)b->n_lat), dim3(kFinishThreads), 0,
                            s, b->lat_commit, nsweeps - 1, nsweeps, hyper);
@@ -4236,7 +4252,8 @@ void make_side_stream(gmrf_batch *b)
         (is_lattice(c->g) ? lattices : graphs) = true;
     if (!lattices || !graphs)
         return;
-    if (hipEventCreateWithFlags(&b->side_start, hipEventDisableTiming) != hipSuccess ||
+    if (hipGetDevice(&b->side_device) != hipSuccess ||
+        hipEventCreateWithFlags(&b->side_start, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&b->side_end, hipEventDisableTiming) != hipSuccess ||
         hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking) != hipSuccess) {
         b->side = nullptr;
