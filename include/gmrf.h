@@ -141,9 +141,10 @@ typedef struct {
                                2: the sites of each color, ranked by original id, share
                                one block per rank pair (2m, 2m + 1): cosine branch for
                                the first, sine branch for the second (Box-Muller's two
-                               independent normals; half the generator work).  Version
-                               2 is taken by Gaussian lattice chains whose width is a
-                               multiple of 4, swept on their own (not in a batch). */
+                               independent normals; each site computes its block, so
+                               both versions cost the same).  Version 2 is taken by
+                               Gaussian lattice chains whose width is a multiple of
+                               4, swept on their own (not in a batch). */
 } gmrf_model;
 
 #define GMRF_GAUSSIAN 0
@@ -402,9 +403,10 @@ int gmrf_set_trace(gmrf_chain *c, double *d_trace, int64_t capacity, hipStream_t
  * chain moves to or from shape 1 with the field in the other buffer, copies the
  * field over (synchronising the device); a batch keeps the shapes its chains
  * had when it was created (shape 2 is batched as shape 0).
- * For a shape-2 chain gmrf_sweep_timed reports the duration of the single
- * launch (draws included) as both kernel and span time (binomial: the
- * Polya-Gamma launches and the one-block launch of each sweep).  Host-only
+ * For a shape-2 chain gmrf_sweep_timed reports the time from the start of the
+ * call's first launch to the end of its last (draws included) as both kernel
+ * and span time (binomial: the Polya-Gamma launches and the one-block launch
+ * of each sweep).  Host-only
  * calls. */
 int gmrf_chain_get_tile(const gmrf_chain *c, int32_t *tile, int32_t *tile_rows, int32_t *tile_cols,
                         int32_t *threads);

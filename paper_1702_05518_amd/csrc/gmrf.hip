@@ -725,9 +725,11 @@ template <int ST_, int TH_, int TW_, int NT_> struct LatCfg {
 // residency hides the phases' latency: 64 registers, four blocks per CU, so
 // that the 1024 tiles of a 2048 x 2048 lattice are resident at once (32.3
 // against 34.5 us per sweep with six wavefronts FP32, 44.8 against 46.2 with
-// four FP64).  The small tile (one quad) is for lattices that leave CUs idle:
-// registers for its loads and draws in flight instead (512 x 512 FP64 10.1
-// against 11.5 us with eight).
+// four FP64).  At that the kernel spills 2 to 10 registers (12 to 44 bytes per
+// lane; the batched form 6 to 20, 28 to 68 bytes), most with an intercept.
+// The small tile (one quad) is for lattices that leave CUs idle: registers for
+// its loads and draws in flight instead (512 x 512 FP64 10.1 against 11.5 us
+// with eight).
 template <typename Real, typename Cfg> constexpr int kLatWaves = Cfg::NQ == 1 ? 4 : 8;
 
 // Colors whose normals are drawn while the tile's loads are in flight: all of
@@ -888,7 +890,9 @@ struct LatRed {
 // pair, the cosine branch for the first, the sine branch for the second.
 // With the lattice width a multiple of 4 every row holds an even number of
 // sites of each of its colors, so the pairs are (r, c) and (r, c + 2) with bit
-// 1 of c clear, keyed by the id of (r, c).
+// 1 of c clear, keyed by the id of (r, c).  Each of the two computes the block:
+// the draws cost what the plain contract's do (1,833 against 1,805 vector
+// instructions per wavefront, 2048 x 2048 FP64).
 template <typename Real, bool V2>
 __device__ __forceinline__ Real lattice_normal(const SweepArgs &a, unsigned t, int r, int c,
                                                int cols)
@@ -1513,7 +1517,7 @@ __device__ __forceinline__ void lattice_tile(Real *xs, const LatArgs<Real> &la, 
 // V2: the chain draws its site normals by the paired contract
 // (lattice_normal).
 //
-// What bounds it: at 2048 x 2048 neither memory (86 MB per FP32 sweep, ~2.7
+// What bounds it: at 2048 x 2048 neither memory (95 MB per FP32 sweep, 3.1
 // TB/s) nor the vector units (56% of their issue slots, against 76% of 38%
 // more instructions before the quads) but the chain of fold, loads, phases
 // and write-back that every resident block walks through together; larger
@@ -3671,10 +3675,12 @@ void *current_x(const gmrf_chain *c, uint64_t sweep);
 // of kReportBytes, allocated at the first read and kept for the life of the
 // process (one set for all devices).  A read holds a slot from its launch to
 // the end of its synchronisation; when all are held, or the memory could not
-// be had, the read copies to the caller's memory instead.  A state block and
-// the field of 48 x 40 FP64 sites: two copies to unpinned memory, each with
-// its synchronisation, 44 us; one launch into a slot
-// 19.
+// be had, the read copies to the caller's memory instead.  A slot saves the
+// same 11 us or so of a copy whatever the size, so its share falls: state and
+// field of FP64 lattices, copied / through a slot, 48 x 40 44 / 19 us, 128 x
+// 128 38 / 25, 180 x 180 (253 KiB) 44 / 33, 256 x 256 61 / 51, 362 x 362 (1
+// MiB) 96 / 87, 512 x 512 223 / 212.  The line is where it still is a
+// quarter, and the slots together stay at 2 MiB.
 constexpr size_t kReportBytes = 256 << 10;
 constexpr int kReportSlots = 8;
 static_assert(sizeof(DevState) % 8 == 0, "the field follows the state block");
