@@ -111,6 +111,7 @@ struct SweepArgs {
     GammaShape g_tau, g_lam;    // Marsaglia-Tsang constants of a_tau + r/2, a_lam + n/2
     double b_tau, b_lam;
     double rho, one_minus_rho;
+    int proper;                 // rho != 1
     long long burn_in;
     unsigned long long seed;
     unsigned int instance;
@@ -669,6 +670,7 @@ template <typename Real> struct SiteCtx {
     Real inv_q_full, isd_full;  // 1/Qii and Qii^-1/2 of a site with all k neighbours
     const Real *qtab;           // LDS: 1/Qii for degree 0 .. ST, then Qii^-1/2 (qtab_fill)
     double one_minus_rho, rho;
+    int proper;                 // rho != 1
 };
 
 // Tile geometry of the fused lattice kernel: TH x TW sites, NT threads.
@@ -891,7 +893,7 @@ struct LatRed {
 // With the lattice width a multiple of 4 every row holds an even number of
 // sites of each of its colors, so the pairs are (r, c) and (r, c + 2) with bit
 // 1 of c clear, keyed by the id of (r, c).  Each of the two computes the block:
-// the draws cost what the plain contract's do (1,833 against 1,805 vector
+// the draws cost what the plain contract's do (1,842 against 1,809 vector
 // instructions per wavefront, 2048 x 2048 FP64).
 template <typename Real, bool V2>
 __device__ __forceinline__ Real lattice_normal(const SweepArgs &a, unsigned t, int r, int c,
@@ -1293,7 +1295,7 @@ __device__ __forceinline__ Red lattice_phases(Real *xs, QuadRegs<Real, Cfg> &t, 
     // whose squares overflow, still have the q of their edges.
     Red r;
     r.q = sc.rho * rd.edge;
-    if (__builtin_amdgcn_readfirstlane(sc.one_minus_rho != 0.0))
+    if (sc.proper)
         r.q = fma(sc.one_minus_rho, INTERIOR ? (double)Cfg::ST * rd.dsq : rd.dsq, r.q);
     r.sse = rd.sse;
     r.rsum = rd.rsum;
@@ -1343,6 +1345,7 @@ __device__ __forceinline__ SiteCtx<Real> site_ctx(const SweepArgs &a,
     sc.beta0 = B0 ? uniform_value(S.beta0) : 0.0;
     sc.beta0_r = B0 ? (Real)sc.beta0 : (Real)0;
     sc.one_minus_rho = a.one_minus_rho;
+    sc.proper = a.proper;
     sc.rho = a.rho;
     sc.qtab = S.qtab;
     return sc;
@@ -1704,6 +1707,7 @@ __global__ __launch_bounds__(Cfg::NT) void lattice_persistent_kernel(LatArgs<Rea
         sc.inv_q_full = qtab[ST];
         sc.isd_full = qtab[2 * ST + 1];
         sc.one_minus_rho = a.one_minus_rho;
+        sc.proper = a.proper;
         sc.rho = a.rho;
         sc.qtab = qtab;
         // this sweep's normals; the next one's and its unit variates load
@@ -3212,6 +3216,7 @@ SweepArgs make_args(const gmrf_chain *c, unsigned flags)
     a.b_lam = c->model.b_lam;
     a.rho = c->g->h.rho;
     a.one_minus_rho = 1.0 - a.rho;
+    a.proper = a.rho != 1.0;
     a.burn_in = (long long)c->model.burn_in;
     a.seed = c->seed;
     a.instance = c->instance;
