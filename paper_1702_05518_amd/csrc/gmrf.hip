@@ -727,8 +727,8 @@ template <int ST_, int TH_, int TW_, int NT_> struct LatCfg {
 // residency hides the phases' latency: 64 registers, four blocks per CU, so
 // that the 1024 tiles of a 2048 x 2048 lattice are resident at once (32.3
 // against 34.5 us per sweep with six wavefronts FP32, 44.8 against 46.2 with
-// four FP64).  At that the kernel spills 2 to 10 registers (12 to 44 bytes per
-// lane; the batched form 6 to 20, 28 to 68 bytes), most with an intercept.
+// four FP64).  At that the kernel spills 2 to 14 registers (12 to 44 bytes per
+// lane; the batched form 8 to 26, 36 to 68 bytes), most with an intercept.
 // The small tile (one quad) is for lattices that leave CUs idle: registers for
 // its loads and draws in flight instead (512 x 512 FP64 10.1 against 11.5 us
 // with eight).
@@ -1635,15 +1635,16 @@ __global__ __launch_bounds__(kThreads) void lattice_ahead_kernel(Real *z, SweepA
     out[1] = L{v[2], v[3]};
 }
 
-// The normals of the thread's quads (quad[i]: their byte offsets in a sweep's).
+// The normals of the thread's quads in a sweep (byte offsets: quad[i] of the
+// quad in a sweep's, sweep of the sweep's, all below kUnitBatch 4096 Real).
 template <typename Real, typename Cfg>
-__device__ __forceinline__ void load_ahead(Real (&v)[Cfg::NQ][4], const Real *z,
+__device__ __forceinline__ void load_ahead(Real (&v)[Cfg::NQ][4], const Real *z, unsigned sweep,
                                            const unsigned (&quad)[Cfg::NQ])
 {
     using L = typename Pair<Real>::Lds;
 #pragma unroll
     for (int i = 0; i < Cfg::NQ; ++i) {
-        const L *const p = reinterpret_cast<const L *>(at_bytes(z, quad[i]));
+        const L *const p = reinterpret_cast<const L *>(at_bytes(z, sweep + quad[i]));
         const L a = p[0], b = p[1];
         v[i][0] = a.x;
         v[i][1] = a.y;
@@ -1673,16 +1674,17 @@ __global__ __launch_bounds__(Cfg::NT) void lattice_persistent_kernel(LatArgs<Rea
     load_quads<Real, Cfg, false>(q.y, la.y, at);
     load_quads<double, Cfg, false>(s1r, a.s1, at);
     load_quads<double, Cfg, false>(s2r, a.s2, at);
-    const int quads = ahead_quads(la.rows, la.cols);
+    constexpr unsigned kQuad = 4u * (unsigned)sizeof(Real);
+    const unsigned ahead_sweep = kQuad * (unsigned)ahead_quads(la.rows, la.cols);
     unsigned quad[NQ];  // a thread without a quad in the lattice reads the first one's
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
         const int r = quad_row<Cfg>((int)threadIdx.x, i), c = quad_col<Cfg>((int)threadIdx.x);
-        const int q = r < la.rows && c < la.cols ? r / 2 * ((la.cols + 1) / 2) + c / 2 : 0;
-        quad[i] = 4u * (unsigned)sizeof(Real) * (unsigned)q;
+        quad[i] = r < la.rows && c < la.cols
+                      ? kQuad * (unsigned)(r / 2 * ((la.cols + 1) / 2) + c / 2) : 0u;
     }
     Real znext[NQ][4];
-    load_ahead<Real, Cfg>(znext, z, quad);
+    load_ahead<Real, Cfg>(znext, z, 0u, quad);
     // the ring lies outside the lattice: 0
     for (int i = (int)threadIdx.x; i < Cfg::LH * Cfg::LW; i += NT)
         xs[i] = (Real)0;
@@ -1717,7 +1719,7 @@ __global__ __launch_bounds__(Cfg::NT) void lattice_persistent_kernel(LatArgs<Rea
 #pragma unroll
             for (int k = 0; k < 4; ++k)
                 q.z[i][k] = znext[i][k];
-        load_ahead<Real, Cfg>(znext, z + (size_t)min(s + 1, nsweeps - 1) * (4 * quads), quad);
+        load_ahead<Real, Cfg>(znext, z, (unsigned)min(s + 1, nsweeps - 1) * ahead_sweep, quad);
         const UnitDraws u = a.with_hyper && threadIdx.x < 2 ? a.units[2 * s + lane]
                                                             : UnitDraws{0.0, 0.0, false};
         Red rd = lattice_phases<Real, Cfg, false, B0, false>(xs, q, at, sc, [](auto) {});
